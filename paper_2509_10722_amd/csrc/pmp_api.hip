@@ -45,7 +45,7 @@ struct Layout {
     BinnedPlan bp;
     size_t row_ptr, col_idx, col_ptr, row_idx, c, wsig, a, x, b, zs, u, v, y_prev, ps_prev;
     size_t sblk, lblk, spart, lpart, ctl, hist, util, lck_beg, lck_end, lr_row, lr_ck, rpart, npart,
-        total;
+        rsync, total;
     int nsb_max, nlb_max, nlc_max, nlr_max;
 };
 
@@ -129,6 +129,7 @@ Layout plan(int m, int n, long long nnz, size_t sz, int layout)
     L.ctl = take(sizeof(Ctl));
     L.hist = take(sizeof(HistEntry) * kHist);
     L.util = take((size_t)n);
+    L.rsync = take(sizeof(ResSync));
     if (L.binned) {
         const size_t tiles = (size_t)L.bp.P * (size_t)L.bp.Q + 1;
         // 4 entries of padding: the accumulation reads aligned groups of 4
@@ -404,6 +405,17 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
         HIP_TRY(hipStreamSynchronize(s));   // the host vectors go out of scope
     }
     d.binned = L.binned ? 1 : 0;
+    if (!L.binned) {
+        int ll = 0, lr = 0;
+        for (int l = 0; l < m; ++l) ll = std::max(ll, hrow[(size_t)l + 1] - hrow[(size_t)l]);
+        for (int j = 0; j < n; ++j) lr = std::max(lr, hcol[(size_t)j + 1] - hcol[(size_t)j]);
+        d.resident = resident_plan(m, n, ll, lr, sizeof(T));
+        d.rsync = (ResSync *)(ws + L.rsync);
+        if (d.resident) {
+            HIP_TRY(resident_configure<T>());
+            launch_fill_int((int *)d.rsync, 0, sizeof(ResSync) / 4, s);
+        }
+    }
     if (L.binned) {
         // link blocks balanced by nonzeros, stream blocks by count; tile
         // offsets and local indices of the binned message layout
@@ -546,6 +558,11 @@ void enqueue_iterations(pmp_handle *h, int k, hipStream_t s)
 {
     Dev<T> &d = dev_of<T>(h);
     const int adapt = h->prm.adapt_every;
+    if (d.resident) {
+        launch_resident<T>(d, k, 0, adapt, s);
+        h->iter_enq = h->iter_fin = h->iter_enq + k;
+        return;
+    }
     for (int i = 1; i <= k; ++i) {
         const long long it = h->iter_enq + 1;
         const bool check = i == k || (adapt > 0 && it % adapt == 0);
@@ -599,17 +616,25 @@ pmp_status solve_impl(pmp_handle *h, pmp_result *out)
         budget -= align;
     }
     HIP_TRY(hipGetLastError());
-    if (!h->graph_exec) {
+    Dev<T> &d = dev_of<T>(h);
+    // A chunk is a replay of the captured check_every iterations, or, for a
+    // small instance, about a thousand iterations in one launch (which leaves
+    // at the stop rule by itself).
+    const long long per = d.resident ? ce * std::max<long long>(1, 1000 / ce) : ce;
+    if (!d.resident && !h->graph_exec) {
         pmp_status st = build_graph<T>(h);
         if (st != PMP_OK) return st;
     }
-    const long long chunks = budget / ce;
     const long long leftover = budget % ce;
+    const long long whole = budget - leftover;
+    const long long chunks = (whole + per - 1) / per;
     bool done = false;
     long long launched = 0, waited = 0;
     while (!done && waited < chunks) {
         while (launched < chunks && launched - waited < kSlots) {
-            HIP_TRY(hipGraphLaunch(h->graph_exec, s));
+            if (d.resident)
+                launch_resident<T>(d, std::min(per, whole - launched * per), ce, h->prm.adapt_every, s);
+            else HIP_TRY(hipGraphLaunch(h->graph_exec, s));
             const int slot = (int)(launched % kSlots);
             HIP_TRY(hipMemcpyAsync(&h->ctl_host[slot], h->ctl, sizeof(Ctl),
                                    hipMemcpyDeviceToHost, s));
@@ -621,9 +646,11 @@ pmp_status solve_impl(pmp_handle *h, pmp_result *out)
         ++waited;
         if (h->ctl_host[slot].done) done = true;
     }
+    HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(s));
     Ctl c;
-    HIP_TRY(hipMemcpy(&c, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
+    if (waited > 0) c = h->ctl_host[(waited - 1) % kSlots];   // the last chunk's, or the one that was done
+    else HIP_TRY(hipMemcpy(&c, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
     h->iter_enq = h->iter_fin = c.iter;
     if (!c.done && leftover > 0) {
         enqueue_iterations<T>(h, (int)leftover, s);

@@ -138,7 +138,7 @@ __device__ void stream_tile(const BDev<T> &d, int tile, T *sv, double *sred)
     const int s0 = d.st_seg[tile], s1 = d.st_seg[tile + 1];
     const int e0 = di.col_ptr[s0];
     const int cnt = di.col_ptr[s1] - e0;
-    const double rho = d.ictl[inst].rho;
+    const double irho = d.ictl[inst].irho;
     double part = 0.0;
     if (cnt <= kBS && !(s1 - s0 == 1 && cnt > kCap)) {
         gather_stage<T, kBT, kBS>(di.row_idx + e0, di.v, sv, cnt);
@@ -146,7 +146,7 @@ __device__ void stream_tile(const BDev<T> &d, int tile, T *sv, double *sred)
         for (int j = s0 + (int)threadIdx.x; j < s1; j += kBT) {
             const int b = di.col_ptr[j] - e0, e = di.col_ptr[j + 1] - e0;
             const double acc = run_sum<T>(sv, b, e);
-            part += stream_update<T, CHECK>(di, j, e - b, acc, rho);
+            part += stream_update<T, CHECK>(di, j, e - b, acc, irho);
         }
     } else {
         // the first kBlock lanes in the single-instance order
@@ -155,7 +155,7 @@ __device__ void stream_tile(const BDev<T> &d, int tile, T *sv, double *sred)
             for (int k = threadIdx.x; k < cnt; k += kBlock)
                 acc += (double)di.v[ld_stream(di.row_idx + e0 + k)];
         acc = block_sum_n<kBT>(acc, sred);
-        if (threadIdx.x == 0) part = stream_update<T, CHECK>(di, s0, cnt, acc, rho);
+        if (threadIdx.x == 0) part = stream_update<T, CHECK>(di, s0, cnt, acc, irho);
     }
     if (CHECK) {
         part = block_sum_n<kBT>(part, sred);
@@ -376,7 +376,9 @@ __global__ __launch_bounds__(kBT) void k_batch(BDev<T> d, int max_iter, int ce, 
             ss = block_sum_n<kBT>(ss, sred);
             sr = block_sum_n<kBT>(sr, sred);
             sl = block_sum_n<kBT>(sl, sred);
-            if (threadIdx.x == 0) finalize<T>(instance_view(d, i), delta, 1, sr, ss + sl);
+            if (threadIdx.x == 0)
+                finalize(&d.ictl[i], d.hist[(size_t)i * kHist + d.ictl[i].nhist % kHist], delta, 1, sr,
+                         ss + sl);
             __syncthreads();
         }
         if (!grid_sync(d.bar, d.abort, G, d.spin_limit)) return;
@@ -394,9 +396,9 @@ __global__ __launch_bounds__(kBT) void k_batch(BDev<T> d, int max_iter, int ce, 
             for (int l = blockIdx.x * blockDim.x + threadIdx.x; l < d.g.m; l += G * blockDim.x) {
                 const double r = d.ictl[find_instance(d.link_off, d.B, l)].ratio;
                 if (r != 1.0) {
-                    const T ut = (T)((double)d.g.u[l] * r);
+                    T ut = d.g.u[l];
+                    d.g.v[l] = link_rescale<T>(d.g.b[l], ut, r);
                     d.g.u[l] = ut;
-                    d.g.v[l] = (T)((double)d.g.b[l] - (double)ut);
                 }
             }
             if (!grid_sync(d.bar, d.abort, G, d.spin_limit)) return;
@@ -680,6 +682,7 @@ pmp_status batch_init_ctl(pmp_batch *b)
         Ctl &c = h[(size_t)i];
         std::memset(&c, 0, sizeof c);
         c.rho = b->prm.rho0;
+        c.irho = 1.0 / c.rho;
         c.ratio = 1.0;
         c.eps_tol = b->eps_tol[(size_t)i];
         c.mu = b->prm.mu;

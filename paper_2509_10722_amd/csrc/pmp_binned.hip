@@ -298,7 +298,7 @@ PMP_BIN_KERNEL void k_bin_stream(Dev<T> d)
     // indices stay non-temporal.
     accumulate<T, false, false, TIDX>(d.mv, d.six, d.ov[(long long)q * d.P], d.ov[(long long)(q + 1) * d.P], S);
     __syncthreads();
-    const double rho = d.ctl->rho;
+    const double irho = d.ctl->irho;
     double part = 0.0;
     constexpr int G = PMP_BIN_EPI;
     // The per-stream vectors (route length, weight, a) go through
@@ -329,10 +329,9 @@ PMP_BIN_KERNEL void k_bin_stream(Dev<T> d)
             const int i = i0 + g * kBinThreads;
             if (i < ns) {
                 const int j = j0 + i;
-                const T xt = (T)prox_stream((double)L[g] * a[g] + (double)S[i], L[g], w[g], rho,
-                                            d.lo, d.hi, a2[g]);
+                T xt, at;
+                stream_core<T>(a[g], w[g], L[g], (double)S[i], irho, d.lo, d.hi, d.alpha, a2[g], xt, at);
                 const double xn = (double)xt;
-                const T at = (T)(d.alpha * xn + (1.0 - d.alpha) * a[g]);
                 if (MODE == kCheck) {          // dual residual: sum_j L_j (dx_j)^2
                     const double dx = xn - xo[g];
                     part += screen((double)L[g] * dx * dx, (double)at);
@@ -426,9 +425,9 @@ PMP_BIN_KERNEL void k_bin_emit(Dev<T> d, int apply)
         const int l = l0 + i;
         T vt = d.v[l];
         if (ratio != 1.0) {
-            const T ut = (T)((double)d.u[l] * ratio);
+            T ut = d.u[l];
+            vt = link_rescale<T>(d.b[l], ut, ratio);
             d.u[l] = ut;
-            vt = (T)((double)d.b[l] - (double)ut);
             d.v[l] = vt;
         }
         Y[i] = (acc_t)vt;

@@ -108,34 +108,48 @@ __device__ __forceinline__ double run_sum(const T *sh, int b, int e)
     return (s0 + s1) + (s2 + s3);
 }
 
+// The per-stream and per-link updates below are shared by every layout, whose
+// results are to agree bit for bit: the compiler does not contract their
+// expressions (which it would do differently from kernel to kernel), and each
+// fused multiply-add is written out.
+
 // Proximal operator of one traffic stream with L terminals and sum of
-// arguments S (Section III-E), clipped to the box.  wsig > 0: log utility
+// arguments S (Section III-E), clipped to the box; irho = 1 / rho.  wsig > 0: log utility
 // with weight wsig (alpha2 = false) or -w / x with weight wsig (alpha2 =
 // true); wsig < 0: linear utility with weight -wsig.  For S < 0 the log root
 // uses the equal form 2w / (rho (sqrt(S^2 + 4wL/rho) - S)).  The -w / x prox
 // is the positive root of L x^3 - S x^2 - w / rho = 0, reached by Newton's
 // method from max(S/L, 0) + (w / (rho L))^(1/3), where the cubic is
 // nonnegative and convex, so the iterates decrease monotonically.
-__device__ __forceinline__ double prox_stream(double S, int L, double wsig, double rho,
+//
+// FP64 divides and square roots are what the epilogues spend their time on
+// (one wave64 FP64 instruction a clock and CU, about 12 for a divide, 20 for
+// a root): every closed form is one quotient num / den, so a stream costs one
+// divide and, with a log utility, one root (four divides before).
+__device__ __forceinline__ double prox_stream(double S, int L, double wsig, double irho,
                                               double lo, double hi, bool alpha2 = false)
 {
+#pragma clang fp contract(off)
     if (L == 0) return hi;
     double x;
     const double dl = (double)L;
+    const double q = fabs(wsig) * irho;   // w / rho
     if (alpha2) {
-        const double c = wsig / rho;
-        x = (S > 0.0 ? S / dl : 0.0) + cbrt(c / dl);
+        x = (S > 0.0 ? S / dl : 0.0) + cbrt(q / dl);
         for (int it = 0; it < 100; ++it) {
-            const double g = (dl * x - S) * x * x - c;
+            const double g = (dl * x - S) * x * x - q;
             const double nx = x - g / ((3.0 * dl * x - 2.0 * S) * x);
             if (!(nx < x)) break;
             x = nx;
         }
-    } else if (wsig > 0.0) {
-        const double disc = sqrt(S * S + 4.0 * wsig * dl / rho);
-        x = S >= 0.0 ? (S + disc) / (2.0 * dl) : 2.0 * wsig / (rho * (disc - S));
     } else {
-        x = (S - wsig / rho) / dl;
+        double num = S + q, den = dl;     // linear
+        if (wsig > 0.0) {                 // log
+            const double disc = sqrt(__builtin_fma(S, S, 4.0 * (dl * q)));
+            num = S < 0.0 ? 2.0 * q : S + disc;
+            den = S < 0.0 ? disc - S : 2.0 * dl;
+        }
+        x = num / den;
     }
     return fmin(fmax(x, lo), hi);
 }
@@ -155,18 +169,28 @@ __device__ __forceinline__ bool is_alpha2(const Dev<T> &d, int j)
     return d.util != nullptr && d.util[j] == PMP_UTIL_ALPHA2;
 }
 
+// One stream's update: new rate and a from the summed link values.
+template <typename T>
+__device__ __forceinline__ void stream_core(double a, double wsig, int L, double vsum, double irho,
+                                            double lo, double hi, double alpha, bool alpha2, T &xt,
+                                            T &at)
+{
+#pragma clang fp contract(off)
+    const double S = __builtin_fma((double)L, a, vsum);
+    xt = (T)prox_stream(S, L, wsig, irho, lo, hi, alpha2);
+    at = (T)__builtin_fma(alpha, (double)xt, (1.0 - alpha) * a);
+}
+
 template <typename T, bool CHECK>
 __device__ __forceinline__ double stream_update(const Dev<T> &d, int j, int L, double vsum,
-                                                double rho)
+                                                double irho)
 {
-    const double a = (double)d.a[j];
-    const double S = (double)L * a + vsum;
-    const T xt = (T)prox_stream(S, L, (double)d.wsig[j], rho, d.lo, d.hi, is_alpha2(d, j));
-    const double xn = (double)xt;
-    const T at = (T)(d.alpha * xn + (1.0 - d.alpha) * a);
+    T xt, at;
+    stream_core<T>((double)d.a[j], (double)d.wsig[j], L, vsum, irho, d.lo, d.hi, d.alpha,
+                   is_alpha2(d, j), xt, at);
     double part = 0.0;
     if (CHECK) {                       // dual residual: sum_j L_j (dx_j)^2
-        const double dx = xn - (double)d.x[j];
+        const double dx = (double)xt - (double)d.x[j];
         part = screen((double)L * dx * dx, (double)at);
     }
     d.x[j] = xt;
@@ -192,25 +216,21 @@ __device__ __forceinline__ LinkIn link_load(const Dev<T> &d, int l)
     return in;
 }
 
-template <typename T, int MODE, bool WRITE_V = true>
-__device__ __forceinline__ double link_update_in(const Dev<T> &d, int l, int deg, double y,
-                                               const LinkIn &in, double &r2, double &s2)
+// One link's update: new b, u, zs (and v = b - u, returned) and the slack prox
+// ps from the link sum y; a check adds the link's residual terms.
+template <typename T, bool CHECK>
+__device__ __forceinline__ T link_core(double al, int deg, double y, const LinkIn &in, T &bt,
+                                       T &ut, T &zt, double &ps, double &r2, double &s2)
 {
+#pragma clang fp contract(off)
     const double c = in.c, u = in.u, b = in.b, zs = in.zs;
-    const double al = d.alpha;
-    const double ps = fmax(zs - u, -c);                 // slack prox
-    if (d.mu_out) d.mu_out[l] = zs - u > -c ? 1 : 0;    // its branch, for reverse mode
+    ps = fmax(zs - u, -c);                              // slack prox
     const double cnt = (double)deg + 1.0;               // |l| = d_l + 1
     const double pbar = (y + ps) / cnt;                 // link average
-    const T bt = (T)(-al * pbar + (1.0 - al) * b);
-    const T ut = (T)(u + al * pbar);
-    const T zt = (T)(al * (ps - pbar) + (1.0 - al) * zs);
-    d.b[l] = bt;
-    d.zs[l] = zt;
-    d.u[l] = ut;
-    const T vt = (T)((double)bt - (double)ut);
-    if (WRITE_V) d.v[l] = vt;
-    if (MODE == kCheck) {
+    bt = (T)__builtin_fma(-al, pbar, (1.0 - al) * b);
+    ut = (T)__builtin_fma(al, pbar, u);
+    zt = (T)__builtin_fma(al, ps - pbar, (1.0 - al) * zs);
+    if (CHECK) {
         // ||r||^2 = sum_l |l| pbar_l^2 and, with D the change since the
         // previous iteration, the link part of ||s||^2 / rho^2:
         // sum_{j on l} (Dx_j - Dpbar)^2 + (Dps - Dpbar)^2
@@ -222,6 +242,21 @@ __device__ __forceinline__ double link_update_in(const Dev<T> &d, int l, int deg
         r2 += screen(cnt * pbar * pbar, (double)bt + (double)ut + (double)zt);
         s2 += (double)deg * dpb * dpb - 2.0 * dpb * dy + (dps - dpb) * (dps - dpb);
     }
+    return (T)((double)bt - (double)ut);
+}
+
+template <typename T, int MODE, bool WRITE_V = true>
+__device__ __forceinline__ double link_update_in(const Dev<T> &d, int l, int deg, double y,
+                                               const LinkIn &in, double &r2, double &s2)
+{
+    T bt, ut, zt;
+    double ps;
+    const T vt = link_core<T, MODE == kCheck>(d.alpha, deg, y, in, bt, ut, zt, ps, r2, s2);
+    if (d.mu_out) d.mu_out[l] = in.zs - in.u > -in.c ? 1 : 0;   // ps's branch, for reverse mode
+    d.b[l] = bt;
+    d.zs[l] = zt;
+    d.u[l] = ut;
+    if (WRITE_V) d.v[l] = vt;
     if (MODE != kPlain) {
         d.y_prev[l] = y;
         d.ps_prev[l] = ps;
@@ -234,6 +269,15 @@ __device__ __forceinline__ double link_update(const Dev<T> &d, int l, int deg, d
                                             double &r2, double &s2)
 {
     return link_update_in<T, MODE, WRITE_V>(d, l, deg, y, link_load<T, MODE>(d, l), r2, s2);
+}
+
+// A balancing step's rescale u <- (rho_old / rho_new) u (eq. (18)); returns v = b - u.
+template <typename T>
+__device__ __forceinline__ T link_rescale(T b, T &u, double ratio)
+{
+#pragma clang fp contract(off)
+    u = (T)((double)u * ratio);
+    return (T)((double)b - (double)u);
 }
 
 // ---- reverse mode (one reversed iteration; see pmp_adjoint.hip) ------------
@@ -292,11 +336,10 @@ __device__ __forceinline__ void adj_stream_step(const Dev<T> &d, const AdjDev &a
 // sums of squares of p, z and u over all terminals, for the relative part
 // of the stop rule: ||r|| < eps_abs sqrt(J) + eps_rel max(||p||, ||z||) and
 // ||s|| < eps_abs sqrt(J) + eps_rel ||rho u||.
-template <typename T>
-__device__ void finalize(const Dev<T> &d, long long delta, int stop, double sr, double ss,
-                         const double *nrm = nullptr)
+// c: the control block, h: the history entry of this check.
+__device__ inline void finalize(Ctl *c, HistEntry &h, long long delta, int stop, double sr,
+                                double ss, const double *nrm = nullptr)
 {
-    Ctl *c = d.ctl;
     const double rho = c->rho;
     const long long it = c->iter + delta;
     const double r = sqrt(sr);
@@ -313,7 +356,6 @@ __device__ void finalize(const Dev<T> &d, long long delta, int stop, double sr, 
     c->r_norm = r;
     c->s_norm = s;
     c->ratio = 1.0;
-    HistEntry &h = d.hist[c->nhist % kHist];
     h.iter = it;
     h.r_norm = r;
     h.s_norm = s;
@@ -331,6 +373,7 @@ __device__ void finalize(const Dev<T> &d, long long delta, int stop, double sr, 
         else if (s > c->mu * r) rn = rho / c->gamma;
         c->ratio = rho / rn;
         c->rho = rn;
+        c->irho = 1.0 / rn;
     }
 }
 

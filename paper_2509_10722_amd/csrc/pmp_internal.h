@@ -46,6 +46,7 @@ constexpr int kNormBlocks = 256;
 // balancing happens on the device).
 struct Ctl {
     double rho;            // penalty of the next iteration
+    double irho;           // 1 / rho
     double ratio;          // pending u rescale rho_old / rho_new (1 = none)
     double r_norm;         // ||r|| at the last check
     double s_norm;         // ||s|| at the last check
@@ -87,6 +88,17 @@ enum : unsigned {
 // decisions.
 enum LinkMode : int { kPlain = 0, kSave = 1, kCheck = 2 };
 
+// Counters of the on-chip iterations of a small instance (pmp_resident.h),
+// each polled or added to on a line of its own.
+struct ResSync {
+    unsigned cnt[8 * 64];           // workgroups started on each XCD
+    unsigned win, pad0[63];         // XCD + 1 whose workgroups form the group
+    unsigned flag[64];              // last barrier each workgroup has reached
+    unsigned base, pad1[63];        // barriers passed by the launches before
+    unsigned solo, exits, abort, pad2[61];
+    double part[32][8];             // residual partials of a check, per workgroup
+};
+
 // Device pointers of one instance (all inside the caller's workspace).
 template <typename T>
 struct Dev {
@@ -127,6 +139,8 @@ struct Dev {
     // Binned message layout (pmp_binned.hip); P link blocks of at most LB
     // links and Q stream blocks of at most SB streams tile R into P x Q tiles.
     int binned;                     // 1: iterations use the binned kernels
+    int resident;                   // > 0: iterations run on chip in this many workgroups
+    ResSync *rsync;                 // their meeting point (pmp_resident.h)
     int P, Q, LB, SB;
     int SR;                         // stream blocks per dispatch round of the stream pass
     const int *lbs, *sbs;           // [P+1], [Q+1] first link / stream of each block
@@ -265,6 +279,16 @@ void launch_bin_adj_link(const Dev<T> &d, const AdjDev &a, const uint8_t *mu_pre
                          const T *ms, T *my, hipStream_t s);
 template <typename T>
 void launch_bin_adj_emit(const Dev<T> &d, const AdjDev &a, T *my, hipStream_t s);
+
+// Small instances: whole runs of iterations inside one launch of a few
+// workgroups (pmp_resident.h), in the gather layout's sums.  Takes the
+// longest link row and route; returns the workgroups, 0 = use the passes.
+int resident_plan(int m, int n, int longest_link, int longest_route, size_t sz);
+template <typename T>
+hipError_t resident_configure();
+// `iters` iterations; ce > 0: a check with the stop rule at multiples of ce.
+template <typename T>
+void launch_resident(const Dev<T> &d, long long iters, int ce, int adapt, hipStream_t s);
 
 // Batched solve (pmp_batch.hip): many instances concatenated block-diagonally
 // into one global pattern, iterated together by one persistent kernel with

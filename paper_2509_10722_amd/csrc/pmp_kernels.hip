@@ -13,6 +13,7 @@
 // fixed order (no atomics; results are bitwise reproducible).  A segment
 // longer than kCap gets a workgroup of its own that strides over it.
 #include "pmp_device.h"
+#include "pmp_resident.h"
 
 #include <cmath>
 
@@ -42,7 +43,7 @@ __global__ __launch_bounds__(kBlock) void k_stream_pass(Dev<T> d)
     const int s0 = d.sblk[blk], s1 = d.sblk[blk + 1];
     const int e0 = d.col_ptr[s0];
     const int cnt = d.col_ptr[s1] - e0;
-    const double rho = d.ctl->rho;
+    const double irho = d.ctl->irho;
     double part = 0.0;
     if (cnt <= kCap) {
         gather_stage<T>(d.row_idx + e0, d.v, sv, cnt);
@@ -51,14 +52,14 @@ __global__ __launch_bounds__(kBlock) void k_stream_pass(Dev<T> d)
         if (j < s1) {
             const int b = d.col_ptr[j] - e0, e = d.col_ptr[j + 1] - e0;
             const double acc = run_sum<T>(sv, b, e);
-            part = stream_update<T, CHECK>(d, j, e - b, acc, rho);
+            part = stream_update<T, CHECK>(d, j, e - b, acc, irho);
         }
     } else {
         double acc = 0.0;
         for (int k = threadIdx.x; k < cnt; k += kBlock)
             acc += (double)d.v[ld_stream(d.row_idx + e0 + k)];
         acc = block_sum(acc, sred);
-        if (threadIdx.x == 0) part = stream_update<T, CHECK>(d, s0, cnt, acc, rho);
+        if (threadIdx.x == 0) part = stream_update<T, CHECK>(d, s0, cnt, acc, irho);
     }
     if (CHECK) {
         part = block_sum(part, sred);
@@ -174,7 +175,8 @@ __global__ __launch_bounds__(kFinThreads) void k_check_finalize(Dev<T> d, int ns
         nrm[1] = q[1] + q[3];   // sum_(l,j) (a_j + b_l)^2 + sum_l zs^2
         nrm[2] = q[4];          // sum_l (d + 1) u^2
     }
-    if (threadIdx.x == 0) finalize<T>(d, delta, stop, sr, ss, rel ? nrm : nullptr);
+    if (threadIdx.x == 0)
+        finalize(d.ctl, d.hist[d.ctl->nhist % kHist], delta, stop, sr, ss, rel ? nrm : nullptr);
 }
 
 // Norms of a check for the relative stop rule, per workgroup (partials in
@@ -220,9 +222,9 @@ __global__ void k_rescale(Dev<T> d)
     const double ratio = d.ctl->ratio;
     if (ratio == 1.0) return;
     for (int l = blockIdx.x * blockDim.x + threadIdx.x; l < d.m; l += gridDim.x * blockDim.x) {
-        const T ut = (T)((double)d.u[l] * ratio);
+        T ut = d.u[l];
+        d.v[l] = link_rescale<T>(d.b[l], ut, ratio);
         d.u[l] = ut;
-        d.v[l] = (T)((double)d.b[l] - (double)ut);
     }
 }
 
@@ -446,6 +448,7 @@ __global__ void k_ctl_init(Ctl *c, double rho, double eps_tol, double eps_rel, d
                            double gamma, int adapt_every)
 {
     c->rho = rho;
+    c->irho = 1.0 / rho;
     c->ratio = 1.0;
     c->r_norm = 0.0;
     c->s_norm = 0.0;
