@@ -33,25 +33,36 @@ __global__ __launch_bounds__(kBlock) void k_adj_stream(Dev<T> d, AdjDev a, const
 {
     __shared__ double sy[kCap];
     __shared__ double sred[kBlock / 64];
-    const int blk = blockIdx.x;
-    const int s0 = d.sblk[blk], s1 = d.sblk[blk + 1];
-    const int e0 = d.col_ptr[s0];
-    const int cnt = d.col_ptr[s1] - e0;
+    const int4 bk = d.sblk[blockIdx.x];
+    const int s0 = bk.x, s1 = bk.y, e0 = bk.z, cnt = bk.w - bk.z;
     const double rho = d.ctl->rho;
     if (cnt <= kCap) {
-        gather_stage<double>(d.row_idx + e0, a.ybar, sy, cnt);
-        __syncthreads();
-        const int j = s0 + (int)threadIdx.x;
+        GatherStage<double> g;
+        g.load_indices(d.row_idx + e0, cnt);
+        const bool q4 = 4 * (s1 - s0) <= kBlock;
+        const int sub = threadIdx.x & 3, j = s0 + (int)(q4 ? threadIdx.x >> 2 : threadIdx.x);
+        int b = 0, e = 0;
+        AdjStreamIn<T> in;
         if (j < s1) {
-            const int b = d.col_ptr[j] - e0, e = d.col_ptr[j + 1] - e0;
-            adj_stream_step<T>(d, a, xt, j, e - b, run_sum<double>(sy, b, e), last, rho);
+            b = d.col_ptr[j] - e0;
+            e = d.col_ptr[j + 1] - e0;
+            in.load(d, a, xt, j, last);
+        }
+        g.gather(a.ybar, cnt);
+        g.store(sy, cnt);
+        __syncthreads();
+        if (j < s1) {
+            const double acc = q4 ? run_sum4<double>(sy, b, e, sub) : run_sum<double>(sy, b, e);
+            if (!q4 || sub == 0) adj_stream_step<T>(d, a, in, j, e - b, acc, rho);
         }
     } else {
-        double acc = 0.0;
-        for (int k = threadIdx.x; k < cnt; k += kBlock)
-            acc += a.ybar[__builtin_nontemporal_load(d.row_idx + e0 + k)];
-        acc = block_sum(acc, sred);
-        if (threadIdx.x == 0) adj_stream_step<T>(d, a, xt, s0, cnt, acc, last, rho);
+        const double acc = block_sum(strided_sum<double, double>(d.row_idx, a.ybar, e0, e0 + cnt,
+                                                                 [](double t) { return t; }), sred);
+        if (threadIdx.x == 0) {
+            AdjStreamIn<T> in;
+            in.load(d, a, xt, s0, last);
+            adj_stream_step<T>(d, a, in, s0, cnt, acc, rho);
+        }
     }
 }
 
@@ -60,34 +71,45 @@ __global__ __launch_bounds__(kBlock) void k_adj_link(Dev<T> d, AdjDev a, const u
 {
     __shared__ double ss[kCap];
     __shared__ double sred[kBlock / 64];
-    const int blk = blockIdx.x;
-    const int l0 = d.lblk[blk], l1 = d.lblk[blk + 1];
-    const int e0 = d.row_ptr[l0];
-    const int cnt = d.row_ptr[l1] - e0;
-    int l = -1, deg = 0;
+    const int4 bk = d.lblk[blockIdx.x];
+    const int l0 = bk.x, l1 = bk.y, e0 = bk.z, cnt = bk.w - bk.z;
+    int l = l0, deg = 0;
     double acc = 0.0;
+    bool own = false;
+    AdjLinkIn in;
     if (cnt <= kCap) {
-        gather_stage<double>(d.col_idx + e0, a.Sbar, ss, cnt);
+        GatherStage<double> g;
+        g.load_indices(d.col_idx + e0, cnt);
+        const bool q4 = 4 * (l1 - l0) <= kBlock;
+        const int sub = threadIdx.x & 3;
+        l = l0 + (int)(q4 ? threadIdx.x >> 2 : threadIdx.x);
+        own = l < l1 && (!q4 || sub == 0);
+        int b = 0, e = 0;
+        if (l < l1) {
+            b = d.row_ptr[l] - e0;
+            e = d.row_ptr[l + 1] - e0;
+        }
+        if (own) in.load(a, l, mu_prev);
+        g.gather(a.Sbar, cnt);
+        g.store(ss, cnt);
         __syncthreads();
-        if (l0 + (int)threadIdx.x < l1) {
-            l = l0 + (int)threadIdx.x;
-            const int b = d.row_ptr[l] - e0, e = d.row_ptr[l + 1] - e0;
-            acc = run_sum<double>(ss, b, e);
-            deg = e - b;
-        }
+        if (l < l1) acc = q4 ? run_sum4<double>(ss, b, e, sub) : run_sum<double>(ss, b, e);
+        deg = e - b;
     } else {
-        for (int k = threadIdx.x; k < cnt; k += kBlock)
-            acc += a.Sbar[__builtin_nontemporal_load(d.col_idx + e0 + k)];
-        acc = block_sum(acc, sred);
-        if (threadIdx.x == 0) {
-            l = l0;
-            deg = cnt;
-        }
+        acc = block_sum(strided_sum<double, double>(d.col_idx, a.Sbar, e0, e0 + cnt,
+                                                    [](double t) { return t; }), sred);
+        own = threadIdx.x == 0;
+        deg = cnt;
+        if (own) in.load(a, l, mu_prev);
     }
-    if (l >= 0) {
-        a.B[l] += acc;
-        a.U[l] -= acc;
-        if (mu_prev) adj_link_step(a, l, deg, d.alpha, mu_prev[l]);
+    if (!own) return;
+    in.B += acc;
+    in.U -= acc;
+    if (mu_prev) {
+        adj_link_step(a, l, deg, d.alpha, in);
+    } else {
+        a.B[l] = in.B;
+        a.U[l] = in.U;
     }
 }
 
@@ -95,7 +117,11 @@ template <typename T>
 __global__ void k_adj_link_only(Dev<T> d, AdjDev a, const uint8_t *mu)
 {
     for (int l = blockIdx.x * blockDim.x + threadIdx.x; l < d.m; l += gridDim.x * blockDim.x)
-        adj_link_step(a, l, d.row_ptr[l + 1] - d.row_ptr[l], d.alpha, mu[l]);
+    {
+        AdjLinkIn in;
+        in.load(a, l, mu);
+        adj_link_step(a, l, d.row_ptr[l + 1] - d.row_ptr[l], d.alpha, in);
+    }
 }
 
 template <typename T>

@@ -44,7 +44,7 @@ struct Layout {
     bool binned;
     BinnedPlan bp;
     size_t row_ptr, col_idx, col_ptr, row_idx, c, wsig, a, x, b, zs, u, v, y_prev, ps_prev;
-    size_t sblk, lblk, spart, lpart, ctl, hist, util, lck_beg, lck_end, lr_row, lr_ck, rpart, npart,
+    size_t sblk, lblk, spart, lpart, ctl, hist, util, lck, lr_row, lr_ck, rpart, npart,
         rsync, total;
     int nsb_max, nlb_max, nlc_max, nlr_max;
 };
@@ -88,10 +88,12 @@ Layout plan(int m, int n, long long nnz, size_t sz, int layout)
         off = align_up(off + std::max<size_t>(bytes, 1));
         return o;
     };
-    // Greedy blocks: each has kBlock segments or is closed by kCap, so two
-    // consecutive blocks hold more than kCap nonzeros.
-    L.nsb_max = (int)std::min<long long>((long long)n, n / kBlock + 2 * nnz / kCap + 2);
-    L.nlb_max = (int)std::min<long long>((long long)m, m / kBlock + 2 * nnz / kCap + 2);
+    // Greedy blocks: each has block_segments segments or is closed by the
+    // nonzero cap, so two consecutive blocks hold more than the cap.
+    // (a longer segment sits alone and may close the block before it)
+    const long long cap = block_nonzeros(nnz);
+    L.nsb_max = (int)std::min<long long>((long long)n, n / block_segments(n, nnz) + 2 * nnz / cap + 2);
+    L.nlb_max = (int)std::min<long long>((long long)m, m / block_segments(m, nnz) + 2 * nnz / cap + 2);
     L.binned = use_binned(m, n, nnz, sz, layout);
     if (L.binned) {
         L.bp = binned_plan(m, n, nnz);   // bounds; the blocks are cut at setup
@@ -114,14 +116,13 @@ Layout plan(int m, int n, long long nnz, size_t sz, int layout)
     L.v = take((size_t)m * sz);
     L.y_prev = take((size_t)m * 8);
     L.ps_prev = take((size_t)m * 8);
-    L.sblk = take(((size_t)L.nsb_max + 1) * 4);
-    L.lblk = take(((size_t)L.nlb_max + 1) * 4);
+    L.sblk = take((size_t)L.nsb_max * sizeof(int4));
+    L.lblk = take((size_t)L.nlb_max * sizeof(int4));
     L.spart = take((size_t)L.nsb_max * 8);
     L.nlr_max = (int)std::min<long long>((long long)m, nnz / (kCap + 1) + 1);
     L.nlc_max = (int)(nnz / kLongChunk + L.nlr_max + 1);
     L.lpart = take(((size_t)L.nlb_max + L.nlr_max) * 16);
-    L.lck_beg = take((size_t)L.nlc_max * 4);
-    L.lck_end = take((size_t)L.nlc_max * 4);
+    L.lck = take((size_t)L.nlc_max * sizeof(int4));
     L.lr_row = take((size_t)L.nlr_max * 4);
     L.lr_ck = take(((size_t)L.nlr_max + 1) * 4);
     L.rpart = take((size_t)L.nlc_max * 8);
@@ -150,7 +151,8 @@ Layout plan(int m, int n, long long nnz, size_t sz, int layout)
     return L;
 }
 
-std::vector<int> make_blocks(const std::vector<int> &ptr, int count)
+std::vector<int> make_blocks(const std::vector<int> &ptr, int count, int segs = kBlock,
+                             int cap = kCap)
 {
     std::vector<int> blk;
     blk.reserve(count / 64 + 2);
@@ -159,11 +161,11 @@ std::vector<int> make_blocks(const std::vector<int> &ptr, int count)
     while (s < count) {
         int e = s;
         long long cnt = 0;
-        while (e < count && e - s < kBlock && cnt + (ptr[e + 1] - ptr[e]) <= kCap) {
+        while (e < count && e - s < segs && cnt + (ptr[e + 1] - ptr[e]) <= cap) {
             cnt += ptr[e + 1] - ptr[e];
             ++e;
         }
-        if (e == s) e = s + 1;   // a segment longer than kCap on its own
+        if (e == s) e = s + 1;   // a segment longer than cap on its own
         blk.push_back(e);
         s = e;
     }
@@ -214,8 +216,9 @@ struct pmp_handle {
     hipEvent_t ev[kSlots] = {};
     long long iter_enq = 0;        // iterations queued
     long long iter_fin = 0;        // iteration of the last queued check
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t graph_exec = nullptr;
+    // check_every iterations, [1]: the last of them a balancing one
+    hipGraph_t graph[2] = {};
+    hipGraphExec_t graph_exec[2] = {};
     // reverse mode (pmp_forward_ckpt / pmp_backward)
     char *adj_ws = nullptr;
     size_t adj_bytes = 0;
@@ -295,12 +298,11 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
     d.v = (T *)(ws + L.v);
     d.y_prev = (double *)(ws + L.y_prev);
     d.ps_prev = (double *)(ws + L.ps_prev);
-    d.sblk = (int *)(ws + L.sblk);
-    d.lblk = (int *)(ws + L.lblk);
+    d.sblk = (const int4 *)(ws + L.sblk);
+    d.lblk = (const int4 *)(ws + L.lblk);
     d.spart = (double *)(ws + L.spart);
     d.lpart = (double *)(ws + L.lpart);
-    d.lck_beg = (int *)(ws + L.lck_beg);
-    d.lck_end = (int *)(ws + L.lck_end);
+    d.lck = (const int4 *)(ws + L.lck);
     d.lr_row = (int *)(ws + L.lr_row);
     d.lr_ck = (int *)(ws + L.lr_ck);
     d.rpart = (double *)(ws + L.rpart);
@@ -363,29 +365,40 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
     HIP_TRY(hipStreamSynchronize(s));
     if (hc.flags & ~kHasAlpha2)
         return fail(PMP_ERR_INVALID, "invalid problem: %s", flag_text(hc.flags).c_str());
-    std::vector<int> sblk = make_blocks(hcol, n), lblk = make_blocks(hrow, m);
-    d.nsb = (int)sblk.size() - 1;
-    d.nlb = (int)lblk.size() - 1;
+    auto blocks = [&](const std::vector<int> &ptr, int count) {
+        const std::vector<int> b = make_blocks(ptr, count, block_segments(count, nnz), block_nonzeros(nnz));
+        std::vector<int4> t;
+        t.reserve(b.size());
+        for (size_t i = 0; i + 1 < b.size(); ++i)
+            t.push_back(make_int4(b[i], b[i + 1], ptr[(size_t)b[i]], ptr[(size_t)b[i + 1]]));
+        return t;
+    };
+    std::vector<int4> sblk = blocks(hcol, n), lblk = blocks(hrow, m);
+    d.nsb = (int)sblk.size();
+    d.nlb = (int)lblk.size();
     if (d.nsb > L.nsb_max || d.nlb > L.nlb_max)
         return fail(PMP_ERR_SHAPE, "internal: block tables exceed their bound");
-    HIP_TRY(hipMemcpyAsync((void *)d.sblk, sblk.data(), sblk.size() * 4, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync((void *)d.lblk, lblk.data(), lblk.size() * 4, hipMemcpyHostToDevice, s));
+    if (d.nsb) HIP_TRY(hipMemcpyAsync((void *)d.sblk, sblk.data(), sblk.size() * sizeof(int4), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync((void *)d.lblk, lblk.data(), lblk.size() * sizeof(int4), hipMemcpyHostToDevice, s));
     {
-        // rows longer than kCap: chunks of kLongChunk nonzeros
-        std::vector<int> cb, ce, lr, lck{0};
+        // rows longer than kCap: chunks of kLongChunk nonzeros, the rows of
+        // several chunks first
+        std::vector<int4> ck;
+        std::vector<int> lr, lck{0};
         long long maxlong = 0;
-        for (int l = 0; l < m; ++l) {
-            const int b = hrow[(size_t)l], e = hrow[(size_t)l + 1];
-            if (e - b <= kCap) continue;
-            maxlong = std::max<long long>(maxlong, e - b);
-            for (int k = b; k < e; k += kLongChunk) {
-                cb.push_back(k);
-                ce.push_back(std::min(e, k + kLongChunk));
+        for (int pass = 0; pass < 2; ++pass) {
+            for (int l = 0; l < m; ++l) {
+                const int b = hrow[(size_t)l], e = hrow[(size_t)l + 1];
+                if (e - b <= kCap || (e - b > kLongChunk) != (pass == 0)) continue;
+                maxlong = std::max<long long>(maxlong, e - b);
+                for (int k = b; k < e; k += kLongChunk)
+                    ck.push_back(make_int4(k, std::min(e, k + kLongChunk), pass ? l : -1, (int)lr.size()));
+                lr.push_back(l);
+                if (!pass) lck.push_back((int)ck.size());
             }
-            lr.push_back(l);
-            lck.push_back((int)cb.size());
+            if (!pass) d.nlm = (int)lr.size();
         }
-        d.nlc = (int)cb.size();
+        d.nlc = (int)ck.size();
         d.nlr = (int)lr.size();
         // Long rows in fixed point (FP32, finite box): with F chosen so that
         // (longest row) x hi x 2^F <= 2^62, every term and every partial sum
@@ -397,8 +410,7 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
         if (d.nlc > L.nlc_max || d.nlr > L.nlr_max)
             return fail(PMP_ERR_SHAPE, "internal: long-row tables exceed their bound");
         if (d.nlc) {
-            HIP_TRY(hipMemcpyAsync((void *)d.lck_beg, cb.data(), cb.size() * 4, hipMemcpyHostToDevice, s));
-            HIP_TRY(hipMemcpyAsync((void *)d.lck_end, ce.data(), ce.size() * 4, hipMemcpyHostToDevice, s));
+            HIP_TRY(hipMemcpyAsync((void *)d.lck, ck.data(), ck.size() * sizeof(int4), hipMemcpyHostToDevice, s));
             HIP_TRY(hipMemcpyAsync((void *)d.lr_row, lr.data(), lr.size() * 4, hipMemcpyHostToDevice, s));
             HIP_TRY(hipMemcpyAsync((void *)d.lr_ck, lck.data(), lck.size() * 4, hipMemcpyHostToDevice, s));
         }
@@ -524,13 +536,13 @@ void stream_pass(const Dev<T> &d, int mode, hipStream_t s)
 // The link pass; a check also reduces its residual partials and decides
 // (stop rule, rho balancing) right after it.
 template <typename T>
-void link_pass(const Dev<T> &d, int mode, long long delta, int stop, hipStream_t s)
+void link_pass(const Dev<T> &d, int mode, long long delta, int stop, bool rel, hipStream_t s)
 {
     if (d.binned) launch_bin_link<T>(d, mode, s);
     else launch_link_pass<T>(d, mode, s);
     if (mode == kCheck)
         launch_check_finalize<T>(d, d.binned ? d.Q : d.nsb, d.binned ? d.P : d.nlb + d.nlr, delta,
-                                 stop, s);
+                                 stop, rel, s);
 }
 
 // After a check iteration: the u rescale of a balancing step, which only
@@ -569,7 +581,7 @@ void enqueue_iterations(pmp_handle *h, int k, hipStream_t s)
         const bool next_check = i < k && (i + 1 == k || (adapt > 0 && (it + 1) % adapt == 0));
         const int mode = check ? kCheck : (next_check ? kSave : kPlain);
         stream_pass<T>(d, mode, s);
-        link_pass<T>(d, mode, it - h->iter_fin, 0, s);
+        link_pass<T>(d, mode, it - h->iter_fin, 0, h->prm.eps_rel > 0.0, s);
         if (check) {
             h->iter_fin = it;
             after_check<T>(d, adapt > 0 && it % adapt == 0, s);
@@ -579,8 +591,11 @@ void enqueue_iterations(pmp_handle *h, int k, hipStream_t s)
 }
 
 // One graph = check_every iterations ending in a check with the stop test.
+// Only the graph of a chunk that ends in a balancing iteration carries the
+// rescale of u, and only a relative stop rule its norm pass: a launch that
+// has nothing to do still takes 2-3 us between two others.
 template <typename T>
-pmp_status build_graph(pmp_handle *h)
+pmp_status build_graph(pmp_handle *h, bool balance)
 {
     Dev<T> &d = dev_of<T>(h);
     const int ce = h->prm.check_every;
@@ -589,15 +604,24 @@ pmp_status build_graph(pmp_handle *h)
         const bool check = i == ce;
         const int mode = check ? kCheck : (i == ce - 1 ? kSave : kPlain);
         stream_pass<T>(d, mode, h->cap_stream);
-        link_pass<T>(d, mode, ce, 1, h->cap_stream);
+        link_pass<T>(d, mode, ce, 1, h->prm.eps_rel > 0.0, h->cap_stream);
     }
-    if (d.binned) launch_bin_emit<T>(d, 1, h->cap_stream);
-    else launch_rescale<T>(d, h->cap_stream);
+    after_check<T>(d, balance, h->cap_stream);
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamEndCapture(h->cap_stream, &g));
-    h->graph = g;
-    HIP_TRY(hipGraphInstantiateWithFlags(&h->graph_exec, g, 0));
+    h->graph[balance] = g;
+    HIP_TRY(hipGraphInstantiateWithFlags(&h->graph_exec[balance], g, 0));
     return PMP_OK;
+}
+
+void drop_graphs(pmp_handle *h)
+{
+    for (int k = 0; k < 2; ++k) {
+        if (h->graph_exec[k]) (void)hipGraphExecDestroy(h->graph_exec[k]);
+        if (h->graph[k]) (void)hipGraphDestroy(h->graph[k]);
+        h->graph_exec[k] = nullptr;
+        h->graph[k] = nullptr;
+    }
 }
 
 template <typename T>
@@ -621,10 +645,6 @@ pmp_status solve_impl(pmp_handle *h, pmp_result *out)
     // small instance, about a thousand iterations in one launch (which leaves
     // at the stop rule by itself).
     const long long per = d.resident ? ce * std::max<long long>(1, 1000 / ce) : ce;
-    if (!d.resident && !h->graph_exec) {
-        pmp_status st = build_graph<T>(h);
-        if (st != PMP_OK) return st;
-    }
     const long long leftover = budget % ce;
     const long long whole = budget - leftover;
     const long long chunks = (whole + per - 1) / per;
@@ -634,7 +654,15 @@ pmp_status solve_impl(pmp_handle *h, pmp_result *out)
         while (launched < chunks && launched - waited < kSlots) {
             if (d.resident)
                 launch_resident<T>(d, std::min(per, whole - launched * per), ce, h->prm.adapt_every, s);
-            else HIP_TRY(hipGraphLaunch(h->graph_exec, s));
+            else {
+                const long long end = start + align + (launched + 1) * ce;
+                const bool balance = h->prm.adapt_every > 0 && end % h->prm.adapt_every == 0;
+                if (!h->graph_exec[balance]) {
+                    const pmp_status st = build_graph<T>(h, balance);
+                    if (st != PMP_OK) return st;
+                }
+                HIP_TRY(hipGraphLaunch(h->graph_exec[balance], s));
+            }
             const int slot = (int)(launched % kSlots);
             HIP_TRY(hipMemcpyAsync(&h->ctl_host[slot], h->ctl, sizeof(Ctl),
                                    hipMemcpyDeviceToHost, s));
@@ -780,7 +808,7 @@ pmp_status forward_ckpt_impl(pmp_handle *h, int K, int s, char *ws, double *J)
             if ((rc = copy_state<T>(h, ws + L.ckpt + (size_t)((t - 1) / s) * L.state, true)) != PMP_OK)
                 return rc;
         stream_pass<T>(d, t == K ? kSave : kPlain, st);   // x^K stored
-        link_pass<T>(d, kPlain, 0, 0, st);
+        link_pass<T>(d, kPlain, 0, 0, false, st);
     }
     // the K iterations count like any others (no check ran among them)
     h->iter_enq += K;
@@ -834,7 +862,7 @@ pmp_status backward_impl(pmp_handle *h, T *gc, T *gw)
             if (h->n) dt.x = tape_x + (size_t)(t - t0 - 1) * h->n;
             dt.mu_out = tape_mu + (size_t)(t - t0 - 1) * h->m;
             stream_pass<T>(dt, kSave, st);
-            link_pass<T>(dt, kPlain, 0, 0, st);
+            link_pass<T>(dt, kPlain, 0, 0, false, st);
         }
         if (t1 < K) {   // link step of iteration t1, deferred from the later segment
             launch_adj_link_only<T>(d, a, tape_mu + (size_t)(t1 - t0 - 1) * h->m, st);
@@ -936,7 +964,7 @@ pmp_status time_kernels_impl(pmp_handle *h, int k, double *ms)
         (void)hipEventRecord(ev[3 * (i - 1)], s);
         stream_pass<T>(d, mode, s);
         (void)hipEventRecord(ev[3 * (i - 1) + 1], s);
-        link_pass<T>(d, mode, it - h->iter_fin, 0, s);
+        link_pass<T>(d, mode, it - h->iter_fin, 0, h->prm.eps_rel > 0.0, s);
         if (check) {
             h->iter_fin = it;
             after_check<T>(d, adapt > 0 && it % adapt == 0, s);
@@ -1231,6 +1259,7 @@ pmp_status pmp_update_params(pmp_handle *h, const pmp_params *params)
     if (params->alpha != h->prm.alpha || params->check_every != h->prm.check_every ||
         params->adapt_every != h->prm.adapt_every || params->layout != h->prm.layout)
         return fail(PMP_ERR_INVALID, "alpha, check_every, adapt_every and layout are fixed at setup");
+    if ((h->prm.eps_rel > 0.0) != (params->eps_rel > 0.0)) drop_graphs(h);   // the norm pass comes or goes
     h->prm.eps_abs = params->eps_abs;
     h->prm.eps_rel = params->eps_rel;
     h->prm.mu = params->mu;
@@ -1321,8 +1350,7 @@ pmp_status pmp_get_layout(pmp_handle *h, int32_t *layout)
 pmp_status pmp_destroy(pmp_handle *h)
 {
     if (!h) return PMP_OK;
-    if (h->graph_exec) (void)hipGraphExecDestroy(h->graph_exec);
-    if (h->graph) (void)hipGraphDestroy(h->graph);
+    drop_graphs(h);
     for (auto &e : h->ev)
         if (e) (void)hipEventDestroy(e);
     if (h->ctl_host) (void)hipHostFree(h->ctl_host);

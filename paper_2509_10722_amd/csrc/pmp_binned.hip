@@ -461,8 +461,9 @@ PMP_BIN_KERNEL void k_bin_adj_stream(Dev<T> d, AdjDev a, const T *xt, int last,
     for (int i = threadIdx.x; i < ns; i += kBinThreads) {
         const int j = j0 + i;
         const int L = d.rlen ? (int)d.rlen[j] : d.col_ptr[j + 1] - d.col_ptr[j];
-        adj_stream_step<T>(d, a, xt, j, L, (double)S[i], last, rho);
-        S[i] = a.Sbar[j];
+        AdjStreamIn<T> in;
+        in.load(d, a, xt, j, last);
+        S[i] = adj_stream_step<T>(d, a, in, j, L, (double)S[i], rho);
     }
     __syncthreads();
     emit_tiles<T>(d.ov + (long long)q * d.P, d.oxq + (long long)q * d.P, d.P, d.six, S, ms);
@@ -485,12 +486,16 @@ PMP_BIN_KERNEL void k_bin_adj_link(Dev<T> d, AdjDev a, const uint8_t *mu_prev, c
     for (int i = threadIdx.x; i < nl; i += kBinThreads) {
         const int l = l0 + i;
         const double vbar = (double)Y[i];
-        a.B[l] += vbar;
-        a.U[l] -= vbar;
+        AdjLinkIn in;
+        in.load(a, l, mu_prev);
+        in.B += vbar;
+        in.U -= vbar;
         if (mu_prev) {
             const int deg = d.dlen ? (int)d.dlen[l] : d.row_ptr[l + 1] - d.row_ptr[l];
-            adj_link_step(a, l, deg, d.alpha, mu_prev[l]);
-            Y[i] = a.ybar[l];
+            Y[i] = adj_link_step(a, l, deg, d.alpha, in);
+        } else {
+            a.B[l] = in.B;
+            a.U[l] = in.U;
         }
     }
     if (!mu_prev) return;   // ybar unchanged: its messages still hold

@@ -63,29 +63,49 @@ __device__ __forceinline__ long long block_sum_ll(long long v, double *sh)
     return r;
 }
 
-// Stage tab[idx[i]] for i < cnt into LDS with a workgroup of NT threads.
-// Every lane first loads its share of the index stream, then issues all of
-// its gathers, then writes LDS, so up to kCap / NT gathers per lane are in
-// flight together.
+// Stage tab[idx[i]] for i < cnt into LDS with a workgroup of NT threads, in
+// three steps so that a caller can issue its other loads between them: load
+// every lane's share of the index stream, issue all its gathers (up to
+// CAP / NT per lane in flight together), write LDS.  Rounds past cnt are
+// skipped by the whole workgroup.
+template <typename T, int NT = kBlock, int CAP = kCap>
+struct GatherStage {
+    static constexpr int R = CAP / NT;
+    int id[R];
+    T val[R];
+    __device__ __forceinline__ void load_indices(const int *__restrict__ idx, int cnt)
+    {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            id[r] = -1;
+            if (r * NT < cnt) {
+                const int i = r * NT + threadIdx.x;
+                if (i < cnt) id[r] = ld_stream(idx + i);
+            }
+        }
+    }
+    __device__ __forceinline__ void gather(const T *__restrict__ tab, int cnt)
+    {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (r * NT < cnt) val[r] = id[r] >= 0 ? tab[id[r]] : T(0);
+    }
+    __device__ __forceinline__ void store(T *sh, int cnt) const
+    {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (r * NT < cnt && id[r] >= 0) sh[r * NT + threadIdx.x] = val[r];
+    }
+};
+
 template <typename T, int NT = kBlock, int CAP = kCap>
 __device__ __forceinline__ void gather_stage(const int *__restrict__ idx,
                                              const T *__restrict__ tab, T *sh, int cnt)
 {
-    constexpr int R = CAP / NT;
-    int id[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int i = r * NT + threadIdx.x;
-        id[r] = i < cnt ? ld_stream(idx + i) : -1;
-    }
-    T val[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) val[r] = id[r] >= 0 ? tab[id[r]] : T(0);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int i = r * NT + threadIdx.x;
-        if (i < cnt) sh[i] = val[r];
-    }
+    GatherStage<T, NT, CAP> g;
+    g.load_indices(idx, cnt);
+    g.gather(tab, cnt);
+    g.store(sh, cnt);
 }
 
 // FP64 sum of sh[b..e) in a fixed order: four interleaved partial sums
@@ -106,6 +126,62 @@ __device__ __forceinline__ double run_sum(const T *sh, int b, int e)
     }
     for (; k < e; ++k) s0 += (double)sh[k];
     return (s0 + s1) + (s2 + s3);
+}
+
+// The same sum by four neighbouring lanes (sub = 0..3), one partial sum each;
+// valid in all four.
+template <typename T>
+__device__ __forceinline__ double run_sum4(const T *sh, int b, int e, int sub)
+{
+    const int body = b + ((e - b) & ~3);
+    double s = 0.0;
+    int k = b + sub;
+    for (; k + 12 < body; k += 16) {
+        const T t0 = sh[k], t1 = sh[k + 4], t2 = sh[k + 8], t3 = sh[k + 12];
+        s += (double)t0;
+        s += (double)t1;
+        s += (double)t2;
+        s += (double)t3;
+    }
+    for (; k < body; k += 4) s += (double)sh[k];
+    if (sub == 0)
+        for (k = body; k < e; ++k) s += (double)sh[k];
+    s += __shfl_xor(s, 1, 64);
+    s += __shfl_xor(s, 2, 64);
+    return s;
+}
+
+// Sum of tab[idx[k]] over k = b + threadIdx.x, + kBlock, ... below e, added in
+// that order, in FP64 or (term: FP64 -> int64) in integers; eight gathers per
+// lane in flight.
+template <typename T, typename A, typename F>
+__device__ __forceinline__ A strided_sum(const int *__restrict__ idx, const T *tab, int b, int e,
+                                         F term)
+{
+    A acc = 0;
+    int k = b + (int)threadIdx.x;
+    for (; k + 7 * kBlock < e; k += 8 * kBlock) {
+        int id[8];
+        T v[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) id[r] = ld_stream(idx + k + r * kBlock);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) v[r] = tab[id[r]];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) acc += term((double)v[r]);
+    }
+    if (k < e) {
+        int id[8];
+        T v[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) id[r] = k + r * kBlock < e ? ld_stream(idx + k + r * kBlock) : -1;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) v[r] = id[r] >= 0 ? tab[id[r]] : T(0);
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            if (id[r] >= 0) acc += term((double)v[r]);
+    }
+    return acc;
 }
 
 // The per-stream and per-link updates below are shared by every layout, whose
@@ -282,33 +358,71 @@ __device__ __forceinline__ T link_rescale(T b, T &u, double ratio)
 
 // ---- reverse mode (one reversed iteration; see pmp_adjoint.hip) ------------
 
-__device__ __forceinline__ void adj_link_step(const AdjDev &a, int l, int deg, double alpha,
-                                          uint8_t mu)
+// Per-link and per-stream inputs of a reversed iteration, loaded ahead of the
+// sums they are combined with.
+struct AdjLinkIn {
+    double B, Z, U, cbar;
+    bool mu;
+    // without a mask (no link step in this kernel) only B and U are needed
+    __device__ __forceinline__ void load(const AdjDev &a, int l, const uint8_t *mask)
+    {
+        B = a.B[l];
+        U = a.U[l];
+        Z = cbar = 0.0;
+        mu = false;
+        if (mask) {
+            Z = a.Z[l];
+            cbar = a.cbar[l];
+            mu = mask[l] != 0;
+        }
+    }
+};
+
+// Returns the link's ybar.
+__device__ __forceinline__ double adj_link_step(const AdjDev &a, int l, int deg, double alpha,
+                                                const AdjLinkIn &in)
 {
-    const double B = a.B[l], Z = a.Z[l], U = a.U[l];
+    const double B = in.B, Z = in.Z, U = in.U;
     const double inv = 1.0 / ((double)deg + 1.0);
     const double pbb = alpha * (U - B - Z);
     const double psb = alpha * Z + pbb * inv;
-    const double m1 = mu ? 1.0 : 0.0;
-    a.ybar[l] = pbb * inv;
-    a.cbar[l] -= (1.0 - m1) * psb;
+    const double m1 = in.mu ? 1.0 : 0.0;
+    const double ybar = pbb * inv;
+    a.ybar[l] = ybar;
+    a.cbar[l] = in.cbar - (1.0 - m1) * psb;
     a.B[l] = (1.0 - alpha) * B;
     a.Z[l] = (1.0 - alpha) * Z + m1 * psb;
     a.U[l] = U - m1 * psb;
+    return ybar;
 }
 
 template <typename T>
-__device__ __forceinline__ void adj_stream_step(const Dev<T> &d, const AdjDev &a, const T *xt,
-                                            int j, int L, double ysum, int last, double rho)
+struct AdjStreamIn {
+    double A, ext, wbar, x, wsig;
+    bool a2;
+    __device__ __forceinline__ void load(const Dev<T> &d, const AdjDev &a, const T *xt, int j, int last)
+    {
+        A = a.A[j];
+        ext = last ? a.ext[j] : 0.0;
+        wbar = a.wbar[j];
+        x = (double)xt[j];
+        wsig = (double)d.wsig[j];
+        a2 = is_alpha2(d, j);
+    }
+};
+
+// Returns the stream's Sbar.
+template <typename T>
+__device__ __forceinline__ double adj_stream_step(const Dev<T> &d, const AdjDev &a,
+                                                  const AdjStreamIn<T> &in, int j, int L,
+                                                  double ysum, double rho)
 {
-    double xbar = d.alpha * a.A[j] + ysum;
-    if (last) xbar += a.ext[j];
-    const double x = (double)xt[j];
-    const double wsig = (double)d.wsig[j];
+    const double xbar = d.alpha * in.A + ysum + in.ext;
+    const double x = in.x, wsig = in.wsig;
     double sbar = 0.0;
     if (L > 0 && x > d.lo && x < d.hi) {
         double dS, dw;
-        if (d.util && d.util[j] == PMP_UTIL_ALPHA2) {
+        if (in.a2) {
             // rho L x^3 - rho S x^2 - w = 0:  dx/dS = rho x^3 / (rho L x^3 + 2w),
             // dx/dw = x / (rho L x^3 + 2w)
             const double den = rho * (double)L * x * x * x + 2.0 * wsig;
@@ -323,10 +437,11 @@ __device__ __forceinline__ void adj_stream_step(const Dev<T> &d, const AdjDev &a
             dw = 1.0 / (rho * (double)L);
         }
         sbar = xbar * dS;
-        a.wbar[j] += xbar * dw;
+        a.wbar[j] = in.wbar + xbar * dw;
     }
-    a.A[j] = (1.0 - d.alpha) * a.A[j] + (double)L * sbar;
+    a.A[j] = (1.0 - d.alpha) * in.A + (double)L * sbar;
     a.Sbar[j] = sbar;
+    return sbar;
 }
 
 // ---- residual reduction, stop rule and rho balancing ---------------------

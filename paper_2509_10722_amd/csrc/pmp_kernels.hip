@@ -33,32 +33,57 @@ __device__ __forceinline__ int xcd_order(int b, int nblocks)
 
 // ---- stream pass ---------------------------------------------------------
 
+// A pass over a small instance is a chain of load latencies, so a workgroup
+// asks for everything as early as it can: its block entry, the done flag and
+// 1 / rho together; then the indices, its segments' pointers and their state;
+// then the gathered values.  Segments of a block that leaves three quarters of
+// the lanes idle are summed by four lanes each (run_sum4).
 template <typename T, bool CHECK>
 __global__ __launch_bounds__(kBlock) void k_stream_pass(Dev<T> d)
 {
-    if (d.ctl->done) return;
     __shared__ T sv[kCap];
     __shared__ double sred[kBlock / 64];
     const int blk = xcd_order((int)blockIdx.x, (int)gridDim.x);
-    const int s0 = d.sblk[blk], s1 = d.sblk[blk + 1];
-    const int e0 = d.col_ptr[s0];
-    const int cnt = d.col_ptr[s1] - e0;
+    const int4 bk = d.sblk[blk];
     const double irho = d.ctl->irho;
+    if (d.ctl->done) return;
+    const int s0 = bk.x, s1 = bk.y, e0 = bk.z, cnt = bk.w - bk.z;
     double part = 0.0;
     if (cnt <= kCap) {
-        gather_stage<T>(d.row_idx + e0, d.v, sv, cnt);
-        __syncthreads();
-        const int j = s0 + (int)threadIdx.x;
+        GatherStage<T> g;
+        g.load_indices(d.row_idx + e0, cnt);
+        const bool q4 = 4 * (s1 - s0) <= kBlock;
+        const int sub = threadIdx.x & 3, j = s0 + (int)(q4 ? threadIdx.x >> 2 : threadIdx.x);
+        int b = 0, e = 0;
+        double a = 0.0, w = 0.0, xo = 0.0;
+        bool a2 = false;
         if (j < s1) {
-            const int b = d.col_ptr[j] - e0, e = d.col_ptr[j + 1] - e0;
-            const double acc = run_sum<T>(sv, b, e);
-            part = stream_update<T, CHECK>(d, j, e - b, acc, irho);
+            b = d.col_ptr[j] - e0;
+            e = d.col_ptr[j + 1] - e0;
+            a = (double)d.a[j];
+            w = (double)d.wsig[j];
+            a2 = is_alpha2(d, j);
+            if (CHECK) xo = (double)d.x[j];
+        }
+        g.gather(d.v, cnt);
+        g.store(sv, cnt);
+        __syncthreads();
+        if (j < s1) {
+            const double acc = q4 ? run_sum4<T>(sv, b, e, sub) : run_sum<T>(sv, b, e);
+            T xt, at;
+            stream_core<T>(a, w, e - b, acc, irho, d.lo, d.hi, d.alpha, a2, xt, at);
+            if (!q4 || sub == 0) {
+                if (CHECK) {
+                    const double dx = (double)xt - xo;
+                    part = screen((double)(e - b) * dx * dx, (double)at);
+                }
+                d.x[j] = xt;
+                d.a[j] = at;
+            }
         }
     } else {
-        double acc = 0.0;
-        for (int k = threadIdx.x; k < cnt; k += kBlock)
-            acc += (double)d.v[ld_stream(d.row_idx + e0 + k)];
-        acc = block_sum(acc, sred);
+        const double acc = block_sum(strided_sum<T, double>(d.row_idx, d.v, e0, e0 + cnt,
+                                                            [](double t) { return t; }), sred);
         if (threadIdx.x == 0) part = stream_update<T, CHECK>(d, s0, cnt, acc, irho);
     }
     if (CHECK) {
@@ -72,41 +97,63 @@ __global__ __launch_bounds__(kBlock) void k_stream_pass(Dev<T> d)
 template <typename T, int MODE>
 __global__ __launch_bounds__(kBlock) void k_link_pass(Dev<T> d)
 {
-    if (d.ctl->done) return;
     __shared__ T sx[kCap];
     __shared__ double sred[kBlock / 64];
-    const int blk = xcd_order((int)blockIdx.x, (int)gridDim.x);
-    if (blk >= d.nlb) {
+    // the chunks of long rows come first, dealt to the XCDs in turn: they are
+    // the longest pieces of work
+    double r2 = 0.0, s2 = 0.0;
+    if ((int)blockIdx.x < d.nlc) {
         // one chunk of a long row: a partial sum in a fixed order, or the
-        // exact fixed-point sum (kept as int64 bits in rpart)
-        const int c = blk - d.nlb;
+        // exact fixed-point sum (kept as int64 bits in rpart); the only chunk
+        // of its row goes on to the link's update
+        const int c = blockIdx.x;
+        const int4 ck = d.lck[c];
+        if (d.ctl->done) return;
+        double y;
         if (d.fx_shift) {
-            long long acc = 0;
-            for (int k = d.lck_beg[c] + threadIdx.x; k < d.lck_end[c]; k += kBlock)
-                acc += fx_term((double)d.x[ld_stream(d.col_idx + k)], d.fx_scale);
-            acc = block_sum_ll(acc, sred);
-            if (threadIdx.x == 0) ((long long *)d.rpart)[c] = acc;
-            return;
+            const double scale = d.fx_scale;
+            const long long acc = block_sum_ll(
+                strided_sum<T, long long>(d.col_idx, d.x, ck.x, ck.y,
+                                          [scale](double t) { return fx_term(t, scale); }), sred);
+            if (threadIdx.x == 0 && ck.z < 0) ((long long *)d.rpart)[c] = acc;
+            y = (double)acc * d.fx_inv;
+        } else {
+            y = block_sum(strided_sum<T, double>(d.col_idx, d.x, ck.x, ck.y,
+                                                 [](double t) { return t; }), sred);
+            if (threadIdx.x == 0 && ck.z < 0) d.rpart[c] = y;
         }
-        double acc = 0.0;
-        for (int k = d.lck_beg[c] + threadIdx.x; k < d.lck_end[c]; k += kBlock)
-            acc += (double)d.x[ld_stream(d.col_idx + k)];
-        acc = block_sum(acc, sred);
-        if (threadIdx.x == 0) d.rpart[c] = acc;
+        if (threadIdx.x == 0 && ck.z >= 0) {
+            link_update<T, MODE>(d, ck.z, ck.y - ck.x, y, r2, s2);
+            if (MODE == kCheck) {
+                d.lpart[2 * (d.nlb + ck.w)] = r2;
+                d.lpart[2 * (d.nlb + ck.w) + 1] = s2;
+            }
+        }
         return;
     }
-    const int l0 = d.lblk[blk], l1 = d.lblk[blk + 1];
-    const int e0 = d.row_ptr[l0];
-    const int cnt = d.row_ptr[l1] - e0;
-    double r2 = 0.0, s2 = 0.0;
+    const int blk = xcd_order((int)blockIdx.x - d.nlc, d.nlb);
+    const int4 bk = d.lblk[blk];
+    if (d.ctl->done) return;
+    const int l0 = bk.x, l1 = bk.y, e0 = bk.z, cnt = bk.w - bk.z;
     if (cnt <= kCap) {
-        gather_stage<T>(d.col_idx + e0, d.x, sx, cnt);
-        __syncthreads();
-        const int l = l0 + (int)threadIdx.x;
+        GatherStage<T> g;
+        g.load_indices(d.col_idx + e0, cnt);
+        const bool q4 = 4 * (l1 - l0) <= kBlock;
+        const int sub = threadIdx.x & 3, l = l0 + (int)(q4 ? threadIdx.x >> 2 : threadIdx.x);
+        const bool own = l < l1 && (!q4 || sub == 0);
+        int b = 0, e = 0;
+        LinkIn in{1.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         if (l < l1) {
-            const int b = d.row_ptr[l] - e0, e = d.row_ptr[l + 1] - e0;
-            const double acc = run_sum<T>(sx, b, e);
-            link_update<T, MODE>(d, l, e - b, acc, r2, s2);
+            b = d.row_ptr[l] - e0;
+            e = d.row_ptr[l + 1] - e0;
+        }
+        if (own) in = link_load<T, MODE>(d, l);
+        g.gather(d.x, cnt);
+        g.store(sx, cnt);
+        __syncthreads();
+        if (l < l1) {
+            const double acc = q4 ? run_sum4<T>(sx, b, e, sub) : run_sum<T>(sx, b, e);
+            if (own) link_update_in<T, MODE>(d, l, e - b, acc, in, r2, s2);
         }
     }
     // a longer row is one of the long rows: its chunks and k_long_rows do it
@@ -120,12 +167,13 @@ __global__ __launch_bounds__(kBlock) void k_link_pass(Dev<T> d)
     }
 }
 
-// Long rows: add each row's chunk sums in chunk order, then the link update.
+// Long rows of several chunks: add each row's chunk sums in chunk order, then
+// the link update.
 template <typename T, int MODE>
 __global__ void k_long_rows(Dev<T> d)
 {
     if (d.ctl->done) return;
-    for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < d.nlr; r += gridDim.x * blockDim.x) {
+    for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < d.nlm; r += gridDim.x * blockDim.x) {
         const int l = d.lr_row[r];
         double y = 0.0;
         if (d.fx_shift) {
@@ -560,7 +608,7 @@ void launch_link_pass(const Dev<T> &d, int mode, hipStream_t s)
 {
     if (d.nlb == 0) return;
     const int grid = d.nlb + d.nlc;
-    const int lg = d.nlr > 0 ? (d.nlr + 63) / 64 : 0;
+    const int lg = (d.nlm + 63) / 64;
     switch (mode) {
     case kPlain:
         hipLaunchKernelGGL((k_link_pass<T, kPlain>), dim3(grid), dim3(kBlock), 0, s, d);
@@ -579,10 +627,9 @@ void launch_link_pass(const Dev<T> &d, int mode, hipStream_t s)
 
 template <typename T>
 void launch_check_finalize(const Dev<T> &d, int nspart, int nlpart, long long delta, int stop,
-                           hipStream_t s)
+                           bool rel, hipStream_t s)
 {
-    // the norm pass returns at once unless the stop rule has a relative part
-    hipLaunchKernelGGL((k_rel_norms<T>), dim3(kNormBlocks), dim3(kBlock), 0, s, d);
+    if (rel) hipLaunchKernelGGL((k_rel_norms<T>), dim3(kNormBlocks), dim3(kBlock), 0, s, d);
     hipLaunchKernelGGL((k_check_finalize<T>), dim3(1), dim3(kFinThreads), 0, s, d, nspart, nlpart,
                        delta, stop);
 }
@@ -744,7 +791,7 @@ void launch_fill_int(int *p, int value, size_t count, hipStream_t s)
 #define PMP_INSTANTIATE(T)                                                                  \
     template void launch_stream_pass<T>(const Dev<T> &, bool, hipStream_t);                \
     template void launch_link_pass<T>(const Dev<T> &, int, hipStream_t);                   \
-    template void launch_check_finalize<T>(const Dev<T> &, int, int, long long, int,       \
+    template void launch_check_finalize<T>(const Dev<T> &, int, int, long long, int, bool, \
                                            hipStream_t);                                    \
     template void launch_rescale<T>(const Dev<T> &, hipStream_t);                           \
     template void launch_refresh_v<T>(const Dev<T> &, hipStream_t);                         \
