@@ -41,8 +41,10 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
     size_t mx, mv, lix, six, ox, ov, oxq, ovp, lbs, sbs, rlen, dlen;
-    bool binned;
+    bool binned, staged;
     BinnedPlan bp;
+    StagedSide ss, sl;
+    size_t perm_s, desc_s, words_s, perm_l, desc_l, words_l, lsum, st_scratch;
     size_t row_ptr, col_idx, col_ptr, row_idx, c, wsig, a, x, b, zs, u, v, y_prev, ps_prev;
     size_t sblk, lblk, spart, lpart, ctl, hist, util, lck, lr_row, lr_ck, rpart, npart,
         rsync, total;
@@ -100,6 +102,11 @@ Layout plan(int m, int n, long long nnz, size_t sz, int layout)
         L.nsb_max = std::max(L.nsb_max, L.bp.Q);
         L.nlb_max = std::max(L.nlb_max, L.bp.P);
     }
+    L.staged = layout == PMP_LAYOUT_AUTO && staged_plan(m, n, nnz, sz, L.ss, L.sl);
+    if (L.staged) {
+        L.nsb_max = std::max(L.nsb_max, L.ss.R);
+        L.nlb_max = std::max(L.nlb_max, staged_link_parts(m));
+    }
     L.row_ptr = take(((size_t)m + 1) * 4);
     L.col_idx = take((size_t)nnz * 4);
     L.col_ptr = take(((size_t)n + 1) * 4);
@@ -146,6 +153,16 @@ Layout plan(int m, int n, long long nnz, size_t sz, int layout)
         L.sbs = take(((size_t)L.bp.Q + 1) * 4);
         L.rlen = take((size_t)n);
         L.dlen = take((size_t)m);
+    }
+    if (L.staged) {
+        L.perm_s = take(staged_slots(L.ss) * 2);
+        L.desc_s = take(staged_tiles(L.ss) * sizeof(uint4));
+        L.words_s = take(staged_words_cap(nnz) * 4);
+        L.perm_l = take(staged_slots(L.sl) * 2);
+        L.desc_l = take(staged_tiles(L.sl) * sizeof(uint4));
+        L.words_l = take(staged_words_cap(nnz) * 4);
+        L.lsum = take((size_t)L.sl.S * m * 8);
+        L.st_scratch = take((std::max(staged_scratch_ints(L.ss), staged_scratch_ints(L.sl)) + 1) * 4);
     }
     L.total = off;
     return L;
@@ -211,6 +228,7 @@ struct pmp_handle {
     int *prune_scratch = nullptr;  // that device's fixed pruning scratch
     Dev<float> df{};
     Dev<double> dd{};
+    int layout = PMP_LAYOUT_GATHER;   // the layout chosen at setup
     Ctl *ctl = nullptr;            // device
     Ctl *ctl_host = nullptr;       // pinned, kSlots entries
     hipEvent_t ev[kSlots] = {};
@@ -416,7 +434,7 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
         }
         HIP_TRY(hipStreamSynchronize(s));   // the host vectors go out of scope
     }
-    d.binned = L.binned ? 1 : 0;
+    h->layout = L.binned ? PMP_LAYOUT_BINNED : PMP_LAYOUT_GATHER;
     if (!L.binned) {
         int ll = 0, lr = 0;
         for (int l = 0; l < m; ++l) ll = std::max(ll, hrow[(size_t)l + 1] - hrow[(size_t)l]);
@@ -428,7 +446,23 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
             launch_fill_int((int *)d.rsync, 0, sizeof(ResSync) / 4, s);
         }
     }
-    if (L.binned) {
+    if (L.staged && !d.resident && d.nlr == 0) {
+        // (long rows keep their fixed-point sums in the other layouts)
+        d.ss = L.ss;
+        d.sl = L.sl;
+        d.lsum = (double *)(ws + L.lsum);
+        int *scratch = (int *)(ws + L.st_scratch);
+        bool ok = false;
+        HIP_TRY(staged_build(d.ss, col_ptr, row_idx, n, nnz, (uint16_t *)(ws + L.perm_s),
+                             (uint4 *)(ws + L.desc_s), (unsigned *)(ws + L.words_s), scratch, &ok, s));
+        if (ok)
+            HIP_TRY(staged_build(d.sl, row_ptr, col_idx, m, nnz, (uint16_t *)(ws + L.perm_l),
+                                 (uint4 *)(ws + L.desc_l), (unsigned *)(ws + L.words_l), scratch, &ok, s));
+        if (ok) HIP_TRY(staged_configure<T>());
+        d.staged = ok ? 1 : 0;
+    }
+    d.binned = L.binned && !d.staged ? 1 : 0;
+    if (d.binned) {
         // link blocks balanced by nonzeros, stream blocks by count; tile
         // offsets and local indices of the binned message layout
         BinnedPlan bp = L.bp;
@@ -529,7 +563,8 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
 template <typename T>
 void stream_pass(const Dev<T> &d, int mode, hipStream_t s)
 {
-    if (d.binned) launch_bin_stream<T>(d, mode, s);
+    if (d.staged) launch_staged_stream<T>(d, mode == kCheck, s);
+    else if (d.binned) launch_bin_stream<T>(d, mode, s);
     else launch_stream_pass<T>(d, mode == kCheck, s);
 }
 
@@ -538,11 +573,13 @@ void stream_pass(const Dev<T> &d, int mode, hipStream_t s)
 template <typename T>
 void link_pass(const Dev<T> &d, int mode, long long delta, int stop, bool rel, hipStream_t s)
 {
-    if (d.binned) launch_bin_link<T>(d, mode, s);
+    if (d.staged) launch_staged_link<T>(d, mode, s);
+    else if (d.binned) launch_bin_link<T>(d, mode, s);
     else launch_link_pass<T>(d, mode, s);
     if (mode == kCheck)
-        launch_check_finalize<T>(d, d.binned ? d.Q : d.nsb, d.binned ? d.P : d.nlb + d.nlr, delta,
-                                 stop, rel, s);
+        launch_check_finalize<T>(d, d.staged ? d.ss.R : d.binned ? d.Q : d.nsb,
+                                 d.staged ? staged_link_parts(d.m) : d.binned ? d.P : d.nlb + d.nlr,
+                                 delta, stop, rel, s);
 }
 
 // After a check iteration: the u rescale of a balancing step, which only
@@ -709,11 +746,13 @@ struct AdjLayout {
     size_t ckpt, final_state, xK, tape_x, tape_mu, A, Sbar, wbar, ext, B, Z, U, ybar, cbar;
     size_t my, ms;   // binned layout: messages of ybar and Sbar (problem precision)
     size_t part, J, total, state;
+    size_t xstride;   // bytes of one x on the tape (whole 256-byte lines)
     int nck, nobj;
 };
 
-// msgs: message slots of the binned layout (0 for the gather layout)
-AdjLayout adj_plan(int m, int n, long long msgs, int K, int s, size_t sz)
+// ymsgs, smsgs: message slots of the binned layout, or elements of ybar and
+// Sbar in the problem's precision of the staged passes (0 for gathers)
+AdjLayout adj_plan(int m, int n, long long ymsgs, long long smsgs, int K, int s, size_t sz)
 {
     AdjLayout L{};
     size_t off = 0;
@@ -728,7 +767,8 @@ AdjLayout adj_plan(int m, int n, long long msgs, int K, int s, size_t sz)
     L.ckpt = take((size_t)L.nck * L.state);
     L.final_state = take(L.state);
     L.xK = take((size_t)n * sz);
-    L.tape_x = take((size_t)s * n * sz);
+    L.xstride = align_up((size_t)n * sz);
+    L.tape_x = take((size_t)s * L.xstride);
     L.tape_mu = take((size_t)s * m);
     L.A = take((size_t)n * 8);
     L.Sbar = take((size_t)n * 8);
@@ -741,11 +781,11 @@ AdjLayout adj_plan(int m, int n, long long msgs, int K, int s, size_t sz)
     L.cbar = take((size_t)m * 8);
     L.part = take((size_t)L.nobj * 8);
     L.J = take(8);
-    if (msgs > 0) {
-        // messages in the problem's precision, with the 4 slots of padding
+    if (ymsgs > 0) {
+        // in the problem's precision, with the 4 slots of padding
         // that the 4-wide FP32 loads of the accumulation may touch
-        L.my = take((size_t)(msgs + 4) * sz);
-        L.ms = take((size_t)(msgs + 4) * sz);
+        L.my = take((size_t)(ymsgs + 4) * sz);
+        L.ms = take((size_t)(smsgs + 4) * sz);
     }
     L.total = off;
     return L;
@@ -753,8 +793,10 @@ AdjLayout adj_plan(int m, int n, long long msgs, int K, int s, size_t sz)
 
 AdjLayout adj_plan_for(const pmp_handle *h, int K, int s)
 {
-    const int binned = h->dtype == PMP_F32 ? h->df.binned : h->dd.binned;
-    return adj_plan(h->m, h->n, binned ? h->nnz : 0, K, s, h->dtype == PMP_F64 ? 8 : 4);
+    const bool f32 = h->dtype == PMP_F32;
+    const int binned = f32 ? h->df.binned : h->dd.binned, staged = f32 ? h->df.staged : h->dd.staged;
+    return adj_plan(h->m, h->n, staged ? h->m : binned ? h->nnz : 0, staged ? h->n : binned ? h->nnz : 0, K, s,
+                    f32 ? 4 : 8);
 }
 
 template <typename T>
@@ -840,14 +882,18 @@ pmp_status backward_impl(pmp_handle *h, T *gc, T *gw)
     const AdjDev a = adj_views(ws, L);
     hipStream_t st = h->stream;
     pmp_status rc;
-    T *tape_x = (T *)(ws + L.tape_x);
+    auto tape_x = [&](int i) { return (T *)(ws + L.tape_x + (size_t)i * L.xstride); };
     uint8_t *tape_mu = (uint8_t *)(ws + L.tape_mu);
     T *my = (T *)(ws + L.my), *ms = (T *)(ws + L.ms);
     launch_ctl_clear_done(h->ctl, st);
     // adjoint seeds from x^K
     if (h->n) HIP_TRY(hipMemcpyAsync(d.x, ws + L.xK, (size_t)h->n * sizeof(T), hipMemcpyDeviceToDevice, st));
     launch_adj_init<T>(d, a, st);
-    if (d.binned) launch_bin_adj_emit<T>(d, a, my, st);   // ybar = 0
+    auto ybar_messages = [&] {      // after ybar changed outside the sums' own kernels
+        if (d.staged) launch_staged_adj_cast<T>(d, a, my, st);
+        else if (d.binned) launch_bin_adj_emit<T>(d, a, my, st);
+    };
+    ybar_messages();                // ybar = 0
     for (int seg = L.nck - 1; seg >= 0; --seg) {
         const int t0 = seg * s, t1 = std::min(t0 + s, K);
         if ((rc = copy_state<T>(h, ws + L.ckpt + (size_t)seg * L.state, false)) != PMP_OK) return rc;
@@ -859,19 +905,22 @@ pmp_status backward_impl(pmp_handle *h, T *gc, T *gw)
             // the handle's own x is restored from x^K at the end
             // and the link pass records the slack mask mu^t in its tape slot
             Dev<T> dt = d;
-            if (h->n) dt.x = tape_x + (size_t)(t - t0 - 1) * h->n;
+            if (h->n) dt.x = tape_x(t - t0 - 1);
             dt.mu_out = tape_mu + (size_t)(t - t0 - 1) * h->m;
             stream_pass<T>(dt, kSave, st);
             link_pass<T>(dt, kPlain, 0, 0, false, st);
         }
         if (t1 < K) {   // link step of iteration t1, deferred from the later segment
             launch_adj_link_only<T>(d, a, tape_mu + (size_t)(t1 - t0 - 1) * h->m, st);
-            if (d.binned) launch_bin_adj_emit<T>(d, a, my, st);
+            ybar_messages();
         }
         for (int t = t1; t > t0; --t) {
-            const T *xt = tape_x + (size_t)(t - t0 - 1) * h->n;
+            const T *xt = tape_x(t - t0 - 1);
             const uint8_t *mu_prev = t - 1 > t0 ? tape_mu + (size_t)(t - 2 - t0) * h->m : nullptr;
-            if (d.binned) {
+            if (d.staged) {
+                launch_staged_adj_stream<T>(d, a, xt, t == K, my, ms, st);
+                launch_staged_adj_link<T>(d, a, mu_prev, ms, my, st);
+            } else if (d.binned) {
                 launch_bin_adj_stream<T>(d, a, xt, t == K, my, ms, st);
                 launch_bin_adj_link<T>(d, a, mu_prev, ms, my, st);
             } else {
@@ -1342,8 +1391,7 @@ pmp_status pmp_device_views(pmp_handle *h, void **x, void **u, void **a, void **
 pmp_status pmp_get_layout(pmp_handle *h, int32_t *layout)
 {
     if (!h || !layout) return fail(PMP_ERR_INVALID, "NULL argument");
-    const int b = h->dtype == PMP_F32 ? h->df.binned : h->dd.binned;
-    *layout = b ? PMP_LAYOUT_BINNED : PMP_LAYOUT_GATHER;
+    *layout = h->layout;
     return PMP_OK;
 }
 

@@ -117,6 +117,18 @@ struct ResSync {
     double part[32][8];             // residual partials of a check, per workgroup
 };
 
+// One side of the LDS-staged passes (pmp_staged.h): rows (streams or links) in
+// R blocks of RB, their sources in C chunks of CH, CPS of them per workgroup
+// and S workgroups per block.
+struct StagedSide {
+    int R, RB;                      // row blocks, rows each
+    int C, CH, CPS, S;
+    int src;                        // source elements
+    const uint16_t *perm;           // [R][C][waves][64][4] row of a lane in each slice, 0xffff = none
+    const uint4 *desc;              // [R][C][waves] first word / 64, words, mask of the slices' last words
+    const unsigned *idx;            // index words, two entries each
+};
+
 // Device pointers of one instance (all inside the caller's workspace).
 template <typename T>
 struct Dev {
@@ -161,6 +173,9 @@ struct Dev {
     // Binned message layout (pmp_binned.hip); P link blocks of at most LB
     // links and Q stream blocks of at most SB streams tile R into P x Q tiles.
     int binned;                     // 1: iterations use the binned kernels
+    int staged;                     // 1: the passes gather from LDS (pmp_staged.h)
+    StagedSide ss, sl;              // its stream and link side
+    double *lsum;                   // [sl.S m] partial link sums
     int resident;                   // > 0: iterations run on chip in this many workgroups
     ResSync *rsync;                 // their meeting point (pmp_resident.h)
     int P, Q, LB, SB;
@@ -312,6 +327,32 @@ hipError_t resident_configure();
 // `iters` iterations; ce > 0: a check with the stop rule at multiples of ce.
 template <typename T>
 void launch_resident(const Dev<T> &d, long long iters, int ce, int adapt, hipStream_t s);
+
+// Passes that gather from LDS (pmp_staged.h).  staged_plan: the shapes for
+// these sizes; false where the other layouts are the better ones.
+bool staged_plan(int m, int n, long long nnz, size_t sz, StagedSide &ss, StagedSide &sl);
+size_t staged_tiles(const StagedSide &sd);
+size_t staged_slots(const StagedSide &sd);
+size_t staged_words_cap(long long nnz);
+size_t staged_scratch_ints(const StagedSide &sd);
+hipError_t staged_build(StagedSide &sd, const int *ptr, const int *idx, int rows, long long nnz, uint16_t *perm,
+                        uint4 *desc, unsigned *words, int *scratch, bool *ok, hipStream_t s);
+template <typename T>
+hipError_t staged_configure();
+template <typename T>
+void launch_staged_stream(const Dev<T> &d, bool check, hipStream_t s);
+template <typename T>
+void launch_staged_link(const Dev<T> &d, int mode, hipStream_t s);
+int staged_link_parts(int m);   // residual partials of its link pass
+// Reverse mode: yt, st hold ybar and Sbar in the problem's precision.
+template <typename T>
+void launch_staged_adj_stream(const Dev<T> &d, const AdjDev &a, const T *xt, int last, const T *yt, T *st,
+                              hipStream_t s);
+template <typename T>
+void launch_staged_adj_link(const Dev<T> &d, const AdjDev &a, const uint8_t *mu_prev, const T *st, T *yt,
+                            hipStream_t s);
+template <typename T>
+void launch_staged_adj_cast(const Dev<T> &d, const AdjDev &a, T *yt, hipStream_t s);
 
 // Batched solve (pmp_batch.hip): many instances concatenated block-diagonally
 // into one global pattern, iterated together by one persistent kernel with

@@ -14,6 +14,7 @@
 // longer than kCap gets a workgroup of its own that strides over it.
 #include "pmp_device.h"
 #include "pmp_resident.h"
+#include "pmp_staged.h"
 
 #include <cmath>
 
