@@ -162,7 +162,7 @@ Layout plan(int m, int n, long long nnz, size_t sz, int layout)
         L.desc_l = take(staged_tiles(L.sl) * sizeof(uint4));
         L.words_l = take(staged_words_cap(nnz) * 4);
         L.lsum = take((size_t)L.sl.S * m * 8);
-        L.st_scratch = take((std::max(staged_scratch_ints(L.ss), staged_scratch_ints(L.sl)) + 1) * 4);
+        L.st_scratch = take((staged_scratch_ints(L.ss) + staged_scratch_ints(L.sl)) * 4);
     }
     L.total = off;
     return L;
@@ -330,12 +330,13 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
     d.lo = p->lo;
     d.hi = p->hi;
     d.alpha = h->prm.alpha;
+    d.rsync = L.binned ? nullptr : (ResSync *)(ws + L.rsync);
     h->ctl = d.ctl;
 
     const double J = (double)nnz + (double)m;
     launch_ctl_init(d.ctl, h->prm.rho0, h->prm.eps_abs * std::sqrt(J), h->prm.eps_rel, h->prm.mu,
                     h->prm.gamma,
-                    h->prm.adapt_every, s);
+                    h->prm.adapt_every, 0, s);
 
     // Inputs into the workspace.
     const hipMemcpyKind kind =
@@ -353,7 +354,7 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
         w_src = d.wsig;
         u_src = (const uint8_t *)(ws + L.util);
     }
-    launch_validate_csr(row_ptr, col_idx, m, n, nnz, d.ctl, s);
+    launch_check_pattern(row_ptr, col_idx, m, n, nnz, (int *)(ws + L.a), d.ctl, s);
     launch_check_vectors<T>(c_src, w_src, u_src, m, n, d.ctl, s);
     HIP_TRY(hipGetLastError());
     Ctl hc;
@@ -370,45 +371,71 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
     }
 
     // CSC pattern (setup step of the stream pass).
-    launch_transpose(row_ptr, col_idx, m, n, nnz, col_ptr, row_idx, (int *)(ws + L.a), s);
-    launch_check_routes(col_ptr, n, p->hi, d.ctl, s);
+    launch_transpose(row_ptr, col_idx, m, n, nnz, col_ptr, row_idx, (int *)(ws + L.a), p->hi, d.ctl, s);
     launch_init_state<T>(d, c_src, w_src, u_src, s);
     HIP_TRY(hipGetLastError());
-
-    // Workgroup tables from the two pointer arrays.
-    std::vector<int> hrow((size_t)m + 1), hcol((size_t)n + 1);
-    HIP_TRY(hipMemcpyAsync(hrow.data(), row_ptr, hrow.size() * 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(hcol.data(), col_ptr, hcol.size() * 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipMemcpyAsync(&hc, d.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     if (hc.flags & ~kHasAlpha2)
         return fail(PMP_ERR_INVALID, "invalid problem: %s", flag_text(hc.flags).c_str());
-    auto blocks = [&](const std::vector<int> &ptr, int count) {
-        const std::vector<int> b = make_blocks(ptr, count, block_segments(count, nnz), block_nonzeros(nnz));
-        std::vector<int4> t;
-        t.reserve(b.size());
-        for (size_t i = 0; i + 1 < b.size(); ++i)
-            t.push_back(make_int4(b[i], b[i + 1], ptr[(size_t)b[i]], ptr[(size_t)b[i + 1]]));
-        return t;
-    };
-    std::vector<int4> sblk = blocks(hcol, n), lblk = blocks(hrow, m);
-    d.nsb = (int)sblk.size();
-    d.nlb = (int)lblk.size();
-    if (d.nsb > L.nsb_max || d.nlb > L.nlb_max)
-        return fail(PMP_ERR_SHAPE, "internal: block tables exceed their bound");
-    if (d.nsb) HIP_TRY(hipMemcpyAsync((void *)d.sblk, sblk.data(), sblk.size() * sizeof(int4), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync((void *)d.lblk, lblk.data(), lblk.size() * sizeof(int4), hipMemcpyHostToDevice, s));
-    {
+    // Long rows in fixed point (FP32, finite box): with F chosen so that
+    // (longest row) x hi x 2^F <= 2^62, every term and every partial sum
+    // fits an int64.  A quantum 2^-F above 2^-24 (very large hi x row
+    // length) would lose more than FP32 rounding: then FP64 sums are kept.
+    const bool long_rows = hc.longest_link > kCap;
+    d.fx_shift = long_row_shift(sizeof(T), long_rows ? hc.longest_link : 0, p->hi);
+    d.fx_scale = std::ldexp(1.0, d.fx_shift);
+    d.fx_inv = std::ldexp(1.0, -d.fx_shift);
+    h->layout = L.binned ? PMP_LAYOUT_BINNED : PMP_LAYOUT_GATHER;
+    if (!L.binned) {
+        d.resident = resident_plan(m, n, hc.longest_link, hc.longest_route, sizeof(T));
+        if (d.resident) HIP_TRY(resident_configure<T>(d));
+    }
+    if (L.staged && !d.resident && !long_rows) {
+        // (long rows keep their fixed-point sums in the other layouts)
+        d.ss = L.ss;
+        d.sl = L.sl;
+        d.lsum = (double *)(ws + L.lsum);
+        StagedTables ts{col_ptr, row_idx, n, (uint16_t *)(ws + L.perm_s), (uint4 *)(ws + L.desc_s),
+                        (unsigned *)(ws + L.words_s)};
+        StagedTables tl{row_ptr, col_idx, m, (uint16_t *)(ws + L.perm_l), (uint4 *)(ws + L.desc_l),
+                        (unsigned *)(ws + L.words_l)};
+        bool ok = false;
+        HIP_TRY(staged_build(d.ss, ts, d.sl, tl, nnz, (int *)(ws + L.st_scratch), &ok, s));
+        if (ok) HIP_TRY(staged_configure<T>());
+        d.staged = ok ? 1 : 0;
+    }
+    d.binned = L.binned && !d.staged ? 1 : 0;
+    // Only the gather passes need tables made from the pointer arrays on the
+    // host (5e6 nonzeros: 2.5 ms for the copies and the loops over the rows).
+    if (!d.staged && !d.binned) {
+        std::vector<int> hrow((size_t)m + 1), hcol((size_t)n + 1);
+        HIP_TRY(hipMemcpyAsync(hrow.data(), row_ptr, hrow.size() * 4, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipMemcpyAsync(hcol.data(), col_ptr, hcol.size() * 4, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        auto blocks = [&](const std::vector<int> &ptr, int count) {
+            const std::vector<int> b = make_blocks(ptr, count, block_segments(count, nnz), block_nonzeros(nnz));
+            std::vector<int4> t;
+            t.reserve(b.size());
+            for (size_t i = 0; i + 1 < b.size(); ++i)
+                t.push_back(make_int4(b[i], b[i + 1], ptr[(size_t)b[i]], ptr[(size_t)b[i + 1]]));
+            return t;
+        };
+        std::vector<int4> sblk = blocks(hcol, n), lblk = blocks(hrow, m);
+        d.nsb = (int)sblk.size();
+        d.nlb = (int)lblk.size();
+        if (d.nsb > L.nsb_max || d.nlb > L.nlb_max)
+            return fail(PMP_ERR_SHAPE, "internal: block tables exceed their bound");
+        if (d.nsb) HIP_TRY(hipMemcpyAsync((void *)d.sblk, sblk.data(), sblk.size() * sizeof(int4), hipMemcpyHostToDevice, s));
+        HIP_TRY(hipMemcpyAsync((void *)d.lblk, lblk.data(), lblk.size() * sizeof(int4), hipMemcpyHostToDevice, s));
         // rows longer than kCap: chunks of kLongChunk nonzeros, the rows of
         // several chunks first
         std::vector<int4> ck;
         std::vector<int> lr, lck{0};
-        long long maxlong = 0;
-        for (int pass = 0; pass < 2; ++pass) {
+        for (int pass = 0; long_rows && pass < 2; ++pass) {
             for (int l = 0; l < m; ++l) {
                 const int b = hrow[(size_t)l], e = hrow[(size_t)l + 1];
                 if (e - b <= kCap || (e - b > kLongChunk) != (pass == 0)) continue;
-                maxlong = std::max<long long>(maxlong, e - b);
                 for (int k = b; k < e; k += kLongChunk)
                     ck.push_back(make_int4(k, std::min(e, k + kLongChunk), pass ? l : -1, (int)lr.size()));
                 lr.push_back(l);
@@ -418,13 +445,6 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
         }
         d.nlc = (int)ck.size();
         d.nlr = (int)lr.size();
-        // Long rows in fixed point (FP32, finite box): with F chosen so that
-        // (longest row) x hi x 2^F <= 2^62, every term and every partial sum
-        // fits an int64.  A quantum 2^-F above 2^-24 (very large hi x row
-        // length) would lose more than FP32 rounding: then FP64 sums are kept.
-        d.fx_shift = long_row_shift(sizeof(T), maxlong, p->hi);
-        d.fx_scale = std::ldexp(1.0, d.fx_shift);
-        d.fx_inv = std::ldexp(1.0, -d.fx_shift);
         if (d.nlc > L.nlc_max || d.nlr > L.nlr_max)
             return fail(PMP_ERR_SHAPE, "internal: long-row tables exceed their bound");
         if (d.nlc) {
@@ -434,40 +454,38 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
         }
         HIP_TRY(hipStreamSynchronize(s));   // the host vectors go out of scope
     }
-    h->layout = L.binned ? PMP_LAYOUT_BINNED : PMP_LAYOUT_GATHER;
-    if (!L.binned) {
-        int ll = 0, lr = 0;
-        for (int l = 0; l < m; ++l) ll = std::max(ll, hrow[(size_t)l + 1] - hrow[(size_t)l]);
-        for (int j = 0; j < n; ++j) lr = std::max(lr, hcol[(size_t)j + 1] - hcol[(size_t)j]);
-        d.resident = resident_plan(m, n, ll, lr, sizeof(T));
-        d.rsync = (ResSync *)(ws + L.rsync);
-        if (d.resident) {
-            HIP_TRY(resident_configure<T>());
-            launch_fill_int((int *)d.rsync, 0, sizeof(ResSync) / 4, s);
-        }
-    }
-    if (L.staged && !d.resident && d.nlr == 0) {
-        // (long rows keep their fixed-point sums in the other layouts)
-        d.ss = L.ss;
-        d.sl = L.sl;
-        d.lsum = (double *)(ws + L.lsum);
-        int *scratch = (int *)(ws + L.st_scratch);
-        bool ok = false;
-        HIP_TRY(staged_build(d.ss, col_ptr, row_idx, n, nnz, (uint16_t *)(ws + L.perm_s),
-                             (uint4 *)(ws + L.desc_s), (unsigned *)(ws + L.words_s), scratch, &ok, s));
-        if (ok)
-            HIP_TRY(staged_build(d.sl, row_ptr, col_idx, m, nnz, (uint16_t *)(ws + L.perm_l),
-                                 (uint4 *)(ws + L.desc_l), (unsigned *)(ws + L.words_l), scratch, &ok, s));
-        if (ok) HIP_TRY(staged_configure<T>());
-        d.staged = ok ? 1 : 0;
-    }
-    d.binned = L.binned && !d.staged ? 1 : 0;
     if (d.binned) {
         // link blocks balanced by nonzeros, stream blocks by count; tile
         // offsets and local indices of the binned message layout
         BinnedPlan bp = L.bp;
         std::vector<int> lbs((size_t)L.bp.P + 1), sbs((size_t)L.bp.Q + 1);
-        binned_blocks(hrow.data(), m, n, nnz, bp, lbs.data(), sbs.data());
+        // from every step-th row pointer (all of them below 2^16 rows): a link
+        // block then ends at most step rows late, under 1% of its rows
+        int step = (int)std::max<long long>(1, ((long long)m + 65535) / 65536);
+        std::vector<int> hptr;
+        auto rows = [&]() -> pmp_status {
+            const int count = (int)(((long long)m + step - 1) / step) + 1;
+            const int *from = row_ptr;
+            if (step > 1) {      // (the tile offsets' place is free yet)
+                launch_sample(row_ptr, m, step, count, (int *)(ws + L.ox), s);
+                from = (const int *)(ws + L.ox);
+            }
+            hptr.resize((size_t)count);
+            HIP_TRY(hipMemcpyAsync(hptr.data(), from, (size_t)count * 4, hipMemcpyDeviceToHost, s));
+            HIP_TRY(hipStreamSynchronize(s));
+            return PMP_OK;
+        };
+        if (step > 1 && (size_t)((m + step - 1) / step + 1) > (size_t)L.bp.P * (size_t)L.bp.Q) step = 1;
+        pmp_status rs = rows();
+        if (rs != PMP_OK) return rs;
+        if (step == 1 || !binned_blocks_sampled(hptr.data(), (int)hptr.size(), step, m, n, nnz, bp, lbs.data(), sbs.data())) {
+            if (step > 1) {
+                step = 1;
+                bp = L.bp;
+                if ((rs = rows()) != PMP_OK) return rs;
+            }
+            binned_blocks(hptr.data(), m, n, nnz, bp, lbs.data(), sbs.data());
+        }
         if (bp.P > L.bp.P || bp.Q > L.bp.Q || bp.LB > L.bp.LB || bp.SB > L.bp.SB)
             return fail(PMP_ERR_SHAPE, "internal: binned blocks exceed their bound");
         d.P = bp.P;
@@ -490,23 +508,10 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
         d.sbs = (const int *)(ws + L.sbs);
         // one byte per route length / link degree instead of two pointer
         // reads, when they all fit
-        auto lengths = [&](const std::vector<int> &ptr, int count, size_t off,
-                           const uint8_t *&out) -> pmp_status {
-            std::vector<uint8_t> len((size_t)count);
-            out = nullptr;
-            for (int i = 0; i < count; ++i) {
-                const int v = ptr[(size_t)i + 1] - ptr[(size_t)i];
-                if (v > 255) return PMP_OK;
-                len[(size_t)i] = (uint8_t)v;
-            }
-            HIP_TRY(hipMemcpyAsync(ws + off, len.data(), (size_t)count, hipMemcpyHostToDevice, s));
-            HIP_TRY(hipStreamSynchronize(s));   // len goes out of scope
-            out = (const uint8_t *)(ws + off);
-            return PMP_OK;
-        };
-        pmp_status ls = lengths(hcol, n, L.rlen, d.rlen);
-        if (ls == PMP_OK) ls = lengths(hrow, m, L.dlen, d.dlen);
-        if (ls != PMP_OK) return ls;
+        d.rlen = hc.longest_route <= 255 ? (const uint8_t *)(ws + L.rlen) : nullptr;
+        d.dlen = hc.longest_link <= 255 ? (const uint8_t *)(ws + L.dlen) : nullptr;
+        if (d.rlen) launch_lengths(col_ptr, n, (uint8_t *)(ws + L.rlen), s);
+        if (d.dlen) launch_lengths(row_ptr, m, (uint8_t *)(ws + L.dlen), s);
         d.mx = (T *)(ws + L.mx);
         d.mv = (T *)(ws + L.mv);
         d.lix = (const uint16_t *)(ws + L.lix);
@@ -525,7 +530,8 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
                                 (int *)d.mx, d.fx_shift > 0, s);
         } else {
             const size_t tiles = (size_t)d.P * (size_t)d.Q + 1;
-            std::vector<int> hcolidx((size_t)nnz);
+            std::vector<int> hcolidx((size_t)nnz), hrow((size_t)m + 1);
+            HIP_TRY(hipMemcpyAsync(hrow.data(), row_ptr, hrow.size() * 4, hipMemcpyDeviceToHost, s));
             if (nnz) HIP_TRY(hipMemcpyAsync(hcolidx.data(), col_idx, (size_t)nnz * 4, hipMemcpyDeviceToHost, s));
             HIP_TRY(hipStreamSynchronize(s));
             std::vector<int> ox(tiles), ov(tiles);
@@ -551,9 +557,8 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
         }
         if (nnz) HIP_TRY(hipMemsetAsync(d.mv, 0, (size_t)nnz * sizeof(T), s));   // v = 0 at the start
         binned_configure();
-        HIP_TRY(hipStreamSynchronize(s));
     }
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(hipStreamSynchronize(s));   // (host tables and caller arrays may go)
     return PMP_OK;
 }
 
@@ -1274,19 +1279,19 @@ pmp_status pmp_set_state(pmp_handle *h, const void *state)
         HIP_TRY(hipMemcpyAsync(zs, p + n + m, m, hipMemcpyDeviceToDevice, s));
         HIP_TRY(hipMemcpyAsync(u, p + n + 2 * m, m, hipMemcpyDeviceToDevice, s));
     }
+    char tail[16];
     double rho;
     long long it;
-    HIP_TRY(hipMemcpyAsync(&rho, p + n + 3 * m, 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&it, p + n + 3 * m + 8, 8, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(tail, p + n + 3 * m, 16, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    std::memcpy(&rho, tail, 8);
+    std::memcpy(&it, tail + 8, 8);
     if (!(rho > 0.0) || !std::isfinite(rho)) return fail(PMP_ERR_INVALID, "state rho must be > 0");
     if (it < 0) return fail(PMP_ERR_INVALID, "state iteration must be >= 0");
     // Re-seed the control block (keeping the tolerances) and v = b - u.
-    Ctl c;
-    HIP_TRY(hipMemcpyAsync(&c, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    launch_ctl_init(h->ctl, rho, c.eps_tol, c.eps_rel, c.mu, c.gamma, c.adapt_every, s);
-    HIP_TRY(hipMemcpyAsync(&h->ctl->iter, &it, 8, hipMemcpyHostToDevice, s));
+    const double J = (double)h->nnz + (double)h->m;
+    launch_ctl_init(h->ctl, rho, h->prm.eps_abs * std::sqrt(J), h->prm.eps_rel, h->prm.mu, h->prm.gamma,
+                    h->prm.adapt_every, it, s);
     if (h->dtype == PMP_F32) {
         launch_refresh_v<float>(h->df, s);
         refresh_messages<float>(h->df, s);

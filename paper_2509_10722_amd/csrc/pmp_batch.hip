@@ -810,7 +810,9 @@ pmp_status batch_setup_impl(pmp_batch *b, const pmp_problem *pr, const pmp_batch
     b->sperm = (int *)(ws + L.sperm);
     if (N) BATCH_TRY(hipMemcpyAsync(b->sperm, sperm.data(), (size_t)N * 4, hipMemcpyHostToDevice, s));
     BATCH_TRY(hipMemcpyAsync((void *)d.hi, hi.data(), (size_t)B * 8, hipMemcpyHostToDevice, s));
-    launch_transpose(g.row_ptr, g.col_idx, M, N, E, (int *)g.col_ptr, (int *)g.row_idx, (int *)(ws + L.a), s);
+    launch_check_pattern(g.row_ptr, g.col_idx, M, N, E, (int *)(ws + L.a), nullptr, s);
+    launch_transpose(g.row_ptr, g.col_idx, M, N, E, (int *)g.col_ptr, (int *)g.row_idx, (int *)(ws + L.a), 0.0,
+                     nullptr, s);
     launch_init_state<T>(g, g.c, g.wsig, (const uint8_t *)(ws + L.util), s);
     g.util = std::any_of(util.begin(), util.end(), [](uint8_t u) { return u == PMP_UTIL_ALPHA2; })
                  ? (const uint8_t *)(ws + L.util)

@@ -87,6 +87,24 @@ void binned_blocks(const int *row_ptr, int m, int n, long long nnz, BinnedPlan &
     for (int q = 0; q <= q0; ++q) sbs[q] = (int)std::min<long long>((long long)q * sb0, n);
 }
 
+bool binned_blocks_sampled(const int *samples, int count, int step, int m, int n, long long nnz, BinnedPlan &bp,
+                           int *lbs, int *sbs)
+{
+    const BinnedPlan bound = bp;
+    int p0, lb0, q0, sb0;
+    count_blocks(m, n, nnz, p0, lb0, q0, sb0);
+    const int rows = count - 1, cap = row_cap(lb0) / step;
+    // blocks closed by the cap now number up to rows / cap
+    if (cap < 1 || p0 + (rows + cap - 1) / cap + 1 > bound.P) return false;
+    bp.P = cut_blocks(samples, rows, nnz, p0, cap, lbs, bp.LB);
+    for (int p = 0; p <= bp.P; ++p) lbs[p] = (int)std::min<long long>((long long)lbs[p] * step, m);
+    bp.LB *= step;
+    bp.Q = q0;
+    bp.SB = sb0;
+    for (int q = 0; q <= q0; ++q) sbs[q] = (int)std::min<long long>((long long)q * sb0, n);
+    return bp.LB <= bound.LB;
+}
+
 void binned_build_host(const int *row_ptr, const int *col_idx, int m, int n, const BinnedPlan &bp,
                        const int *lbs, const int *sbs, int *ox, int *ov, uint16_t *lix,
                        uint16_t *six, int mark_long)

@@ -77,9 +77,8 @@ struct Ctl {
     int adapt_every;       // 0 = fixed rho
     int done;              // 1: stop rule met or numeric failure
     int status;            // pmp_status of the last check
-    unsigned int arrive;   // arrival counter of the last-workgroup finalize
+    int longest_link, longest_route;   // setup: longest row of R, longest column
     unsigned int flags;    // setup validation error bits
-    int pad;
 };
 
 struct HistEntry {
@@ -277,6 +276,10 @@ BinnedPlan binned_plan(int m, int n, long long nnz);
 // bp to the actual values (within the bounds of binned_plan).
 void binned_blocks(const int *row_ptr, int m, int n, long long nnz, BinnedPlan &bp, int *lbs,
                    int *sbs);
+// The same from every step-th row pointer (count of them, the last one nnz):
+// blocks start at multiples of step.  False where they would exceed the bounds.
+bool binned_blocks_sampled(const int *samples, int count, int step, int m, int n, long long nnz, BinnedPlan &bp,
+                           int *lbs, int *sbs);
 // Host construction of ox, ov, lix, six from the CSR pattern and the blocks.
 // With mark_long, lix entries of rows longer than kCap carry kLongBit.
 void binned_build_host(const int *row_ptr, const int *col_idx, int m, int n, const BinnedPlan &bp,
@@ -323,7 +326,7 @@ void launch_bin_adj_emit(const Dev<T> &d, const AdjDev &a, T *my, hipStream_t s)
 // longest link row and route; returns the workgroups, 0 = use the passes.
 int resident_plan(int m, int n, int longest_link, int longest_route, size_t sz);
 template <typename T>
-hipError_t resident_configure();
+hipError_t resident_configure(const Dev<T> &d);
 // `iters` iterations; ce > 0: a check with the stop rule at multiples of ce.
 template <typename T>
 void launch_resident(const Dev<T> &d, long long iters, int ce, int adapt, hipStream_t s);
@@ -335,8 +338,18 @@ size_t staged_tiles(const StagedSide &sd);
 size_t staged_slots(const StagedSide &sd);
 size_t staged_words_cap(long long nnz);
 size_t staged_scratch_ints(const StagedSide &sd);
-hipError_t staged_build(StagedSide &sd, const int *ptr, const int *idx, int rows, long long nnz, uint16_t *perm,
-                        uint4 *desc, unsigned *words, int *scratch, bool *ok, hipStream_t s);
+// One side's pattern (CSC for streams, CSR for links) and the place of its tables.
+struct StagedTables {
+    const int *ptr, *idx;
+    int rows;
+    uint16_t *perm;
+    uint4 *desc;
+    unsigned *words;
+};
+// Builds both sides' tables; scratch holds both sides' staged_scratch_ints.
+// *ok = false where the pattern is too uneven for them.
+hipError_t staged_build(StagedSide &ss, const StagedTables &ts, StagedSide &sl, const StagedTables &tl, long long nnz,
+                        int *scratch, bool *ok, hipStream_t s);
 template <typename T>
 hipError_t staged_configure();
 template <typename T>
@@ -429,15 +442,20 @@ void launch_adj_out(const Dev<T> &d, const AdjDev &a, T *gc, T *gw, hipStream_t 
 template <typename T>
 void launch_copy_weights(const Dev<T> &d, const T *w_new, hipStream_t s);
 
-void launch_validate_csr(const int *row_ptr, const int *col_idx, int m, int n, long long nnz,
-                         Ctl *ctl, hipStream_t s);
-// CSR -> CSC transpose of the pattern; `tmp` holds n + 1 + scan scratch ints.
+// CSR -> CSC transpose of the pattern in two steps; `tmp` holds
+// transpose_scratch_ints ints.  First the entries of each column (into tmp),
+// with ctl also the checks of the pattern and the longest row; then, once the
+// pattern is known to be valid, the transpose, with ctl also the longest route
+// and the check of empty routes against the box.
 size_t transpose_scratch_ints(int n);
+void launch_check_pattern(const int *row_ptr, const int *col_idx, int m, int n, long long nnz, int *tmp,
+                          Ctl *ctl, hipStream_t s);
 void launch_transpose(const int *row_ptr, const int *col_idx, int m, int n, long long nnz,
-                      int *col_ptr, int *row_idx, int *tmp, hipStream_t s);
-void launch_check_routes(const int *col_ptr, int n, double hi, Ctl *ctl, hipStream_t s);
+                      int *col_ptr, int *row_idx, int *tmp, double hi, Ctl *ctl, hipStream_t s);
+void launch_lengths(const int *ptr, int count, uint8_t *out, hipStream_t s);   // row lengths as bytes
+void launch_sample(const int *ptr, int m, int step, int count, int *out, hipStream_t s);   // every step-th pointer
 void launch_ctl_init(Ctl *ctl, double rho, double eps_tol, double eps_rel, double mu,
-                     double gamma, int adapt_every, hipStream_t s);
+                     double gamma, int adapt_every, long long iter, hipStream_t s);
 void launch_ctl_clear_done(Ctl *ctl, hipStream_t s);
 // Count k iterations run without a check (ctl->iter += k).
 void launch_ctl_advance(Ctl *ctl, long long k, hipStream_t s);

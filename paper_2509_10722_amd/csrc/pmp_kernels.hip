@@ -16,6 +16,7 @@
 #include "pmp_resident.h"
 #include "pmp_staged.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace pmp {
@@ -305,6 +306,9 @@ __global__ void k_init_state(Dev<T> d, const T *c_in, const T *w_in, const uint8
         d.y_prev[l] = 0.0;
         d.ps_prev[l] = 0.0;
     }
+    if (d.rsync)
+        for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < (int)(sizeof(ResSync) / 4); i += stride)
+            ((int *)d.rsync)[i] = 0;
 }
 
 template <typename T>
@@ -344,35 +348,68 @@ __global__ void k_check_vectors(const T *c, const T *w, const uint8_t *util, int
     if (f) atomicOr(&ctl->flags, f);
 }
 
-__global__ void k_validate_csr(const int *row_ptr, const int *col_idx, int m, int n,
-                               long long nnz, Ctl *ctl)
+// Row of entry k: the largest r in [lo, hi) with ptr[r] <= k (empty rows
+// share their pointer with the row after them).
+__device__ __forceinline__ int row_of(const int *ptr, int lo, int hi, long long k)
 {
-    const int stride = gridDim.x * blockDim.x;
-    unsigned f = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        if (row_ptr[0] != 0 || (long long)row_ptr[m] != nnz) f |= kErrRowPtr;
-    for (int l = blockIdx.x * blockDim.x + threadIdx.x; l < m; l += stride) {
-        const long long b = row_ptr[l], e = row_ptr[l + 1];
-        if (b < 0 || e < b || e > nnz) {
-            f |= kErrRowPtr;
-            continue;
-        }
-        int prev = -1;
-        for (long long k = b; k < e; ++k) {
-            const int j = col_idx[k];
-            if (j < 0 || j >= n) f |= kErrColRange;
-            else if (j <= prev) f |= kErrColOrder;
-            prev = j;
-        }
+    while (hi - lo > 1) {
+        const int mid = lo + (hi - lo) / 2;
+        if (ptr[mid] <= k) lo = mid;
+        else hi = mid;
     }
-    if (f) atomicOr(&ctl->flags, f);
+    return lo;
 }
 
-__global__ void k_histogram(const int *col_idx, long long nnz, int *count)
+// Entries of a workgroup that works per nonzero, whatever the rows' lengths
+// (a thread per row takes milliseconds over one row of thousands), and the
+// rows [lo, hi) they lie in.
+constexpr int kEntries = 8 * kBlock;
+__device__ __forceinline__ void entry_rows(const int *ptr, int m, long long e0, long long e1, int *sh)
 {
-    const long long stride = (long long)gridDim.x * blockDim.x;
-    for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < nnz; k += stride)
-        atomicAdd(&count[col_idx[k]], 1);
+    if (threadIdx.x == 0) sh[0] = row_of(ptr, 0, m, e0);
+    if (threadIdx.x == 64) sh[1] = row_of(ptr, 0, m, e1 - 1) + 1;
+    __syncthreads();
+}
+
+// Checks of the pattern (per row and per entry; every read is in bounds
+// whatever the values), the entries of every column, and the longest row.
+// ctl NULL: the counts only.
+__global__ __launch_bounds__(kBlock) void k_check_pattern(const int *row_ptr, const int *col_idx, int m, int n,
+                                                          long long nnz, int *count, Ctl *ctl)
+{
+    __shared__ int sh[2];
+    __shared__ int longest;
+    const long long e0 = (long long)blockIdx.x * kEntries;
+    const long long e1 = e0 + kEntries < nnz ? e0 + kEntries : nnz;
+    unsigned f = 0;
+    if (ctl) {
+        if (threadIdx.x == 0) longest = 0;
+        __syncthreads();
+        const int stride = gridDim.x * blockDim.x;
+        int most = 0;
+        if (blockIdx.x == 0 && threadIdx.x == 0)
+            if (row_ptr[0] != 0 || (long long)row_ptr[m] != nnz) f |= kErrRowPtr;
+        for (int l = blockIdx.x * blockDim.x + threadIdx.x; l < m; l += stride) {
+            const long long b = row_ptr[l], e = row_ptr[l + 1];
+            if (b < 0 || e < b || e > nnz) f |= kErrRowPtr;
+            else most = max(most, (int)(e - b));
+        }
+        atomicMax(&longest, most);
+        __syncthreads();
+        if (threadIdx.x == 0) atomicMax(&ctl->longest_link, longest);
+        if (e0 < nnz) entry_rows(row_ptr, m, e0, e1, sh);
+    }
+    for (long long k = e0 + threadIdx.x; k < e1; k += kBlock) {
+        const int j = col_idx[k];
+        if (j < 0 || j >= n) {
+            f |= kErrColRange;
+            continue;
+        }
+        atomicAdd(&count[j], 1);
+        if (ctl && k > 0 && col_idx[k - 1] >= j && row_ptr[row_of(row_ptr, sh[0], sh[1], k)] != k)
+            f |= kErrColOrder;
+    }
+    if (f && ctl) atomicOr(&ctl->flags, f);
 }
 
 constexpr int kScanPer = 8;                      // elements per thread
@@ -447,22 +484,26 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(const int *in, int n, con
     if (blockIdx.x == 0 && threadIdx.x == 0) out[0] = 0;
 }
 
-__global__ void k_scatter(const int *row_ptr, const int *col_idx, int m, const int *col_ptr,
-                          int *fill, int *row_idx)
+__global__ __launch_bounds__(kBlock) void k_scatter(const int *row_ptr, const int *col_idx, int m, long long nnz,
+                                                    const int *col_ptr, int *fill, int *row_idx)
 {
-    const int stride = gridDim.x * blockDim.x;
-    for (int l = blockIdx.x * blockDim.x + threadIdx.x; l < m; l += stride) {
-        for (int k = row_ptr[l]; k < row_ptr[l + 1]; ++k) {
-            const int j = col_idx[k];
-            row_idx[col_ptr[j] + atomicAdd(&fill[j], 1)] = l;
-        }
+    __shared__ int sh[2];
+    const long long e0 = (long long)blockIdx.x * kEntries;
+    const long long e1 = e0 + kEntries < nnz ? e0 + kEntries : nnz;
+    entry_rows(row_ptr, m, e0, e1, sh);
+    for (long long k = e0 + threadIdx.x; k < e1; k += kBlock) {
+        const int j = col_idx[k];
+        row_idx[col_ptr[j] + atomicAdd(&fill[j], 1)] = row_of(row_ptr, sh[0], sh[1], k);
     }
 }
 
-// Sort every column's links ascending (the scatter order is arbitrary).
-__global__ void k_sort_columns(const int *col_ptr, int n, int *row_idx)
+// Sort every column's links ascending (the scatter order is arbitrary); with
+// ctl, also the longest route, and the error of an empty route without a
+// finite box.
+__global__ void k_sort_columns(const int *col_ptr, int n, int *row_idx, double hi, Ctl *ctl)
 {
     const int stride = gridDim.x * blockDim.x;
+    int most = 0, least = 1;
     for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) {
         const int b = col_ptr[j], e = col_ptr[j + 1];
         for (int i = b + 1; i < e; ++i) {
@@ -474,16 +515,37 @@ __global__ void k_sort_columns(const int *col_ptr, int n, int *row_idx)
             }
             row_idx[k + 1] = key;
         }
+        most = max(most, e - b);
+        least = min(least, e - b);
+    }
+    if (!ctl) return;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        most = max(most, __shfl_xor(most, off, 64));
+        least = min(least, __shfl_xor(least, off, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        // (few waves find a longer route than those before them)
+        if (most > __hip_atomic_load(&ctl->longest_route, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(&ctl->longest_route, most);
+        if (least == 0 && isinf(hi)) atomicOr(&ctl->flags, kErrEmptyRoute);
     }
 }
 
-__global__ void k_check_routes(const int *col_ptr, int n, double hi, Ctl *ctl)
+// out[i] = row length, where all fit a byte.
+__global__ void k_lengths(const int *ptr, int count, uint8_t *out)
 {
-    const int stride = gridDim.x * blockDim.x;
-    unsigned f = 0;
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride)
-        if (col_ptr[j + 1] == col_ptr[j] && isinf(hi)) f |= kErrEmptyRoute;
-    if (f) atomicOr(&ctl->flags, f);
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x)
+        out[i] = (uint8_t)(ptr[i + 1] - ptr[i]);
+}
+
+// out[i] = ptr[min(i step, m)], i < count.
+__global__ void k_sample(const int *ptr, int m, int step, int count, int *out)
+{
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) {
+        const long long k = (long long)i * step;
+        out[i] = ptr[k < m ? k : m];
+    }
 }
 
 __global__ void k_fill_int(int *p, int value, size_t count)
@@ -494,7 +556,7 @@ __global__ void k_fill_int(int *p, int value, size_t count)
 }
 
 __global__ void k_ctl_init(Ctl *c, double rho, double eps_tol, double eps_rel, double mu,
-                           double gamma, int adapt_every)
+                           double gamma, int adapt_every, long long iter)
 {
     c->rho = rho;
     c->irho = 1.0 / rho;
@@ -506,13 +568,13 @@ __global__ void k_ctl_init(Ctl *c, double rho, double eps_tol, double eps_rel, d
     c->p_norm = c->z_norm = c->u_norm = 0.0;
     c->mu = mu;
     c->gamma = gamma;
-    c->iter = 0;
+    c->iter = iter;
     c->nhist = 0;
     c->adapt_every = adapt_every;
     c->done = 0;
     c->status = PMP_OK;
-    c->arrive = 0u;
     c->flags = 0u;
+    c->longest_link = c->longest_route = 0;
 }
 
 __global__ void k_ctl_set_tolerances(Ctl *c, double eps_tol, double eps_rel, double mu,
@@ -702,13 +764,6 @@ void launch_path_prices(const Dev<T> &d, T *pi, hipStream_t s)
                        d, pi);
 }
 
-void launch_validate_csr(const int *row_ptr, const int *col_idx, int m, int n, long long nnz,
-                         Ctl *ctl, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_validate_csr, dim3(grid_for(m, kBlock, 16384)), dim3(kBlock), 0, s,
-                       row_ptr, col_idx, m, n, nnz, ctl);
-}
-
 size_t transpose_scratch_ints(int n)
 {
     const size_t nb = ((size_t)n + kScanTile - 1) / kScanTile;
@@ -732,37 +787,47 @@ void launch_scan_int(const int *in, int n, int *out, int *bsum, hipStream_t s)
     }
 }
 
+void launch_check_pattern(const int *row_ptr, const int *col_idx, int m, int n, long long nnz, int *tmp,
+                          Ctl *ctl, hipStream_t s)
+{
+    launch_fill_int(tmp, 0, (size_t)n, s);
+    const long long rows = ctl ? ((long long)m + 16 * kBlock - 1) / (16 * kBlock) : 0;
+    const long long g = std::max<long long>(std::max<long long>(1, rows), (nnz + kEntries - 1) / kEntries);
+    hipLaunchKernelGGL(k_check_pattern, dim3((unsigned)g), dim3(kBlock), 0, s, row_ptr, col_idx, m, n, nnz, tmp,
+                       ctl);
+}
+
 void launch_transpose(const int *row_ptr, const int *col_idx, int m, int n, long long nnz,
-                      int *col_ptr, int *row_idx, int *tmp, hipStream_t s)
+                      int *col_ptr, int *row_idx, int *tmp, double hi, Ctl *ctl, hipStream_t s)
 {
     int *count = tmp;
     int *bsum = tmp + n;
-    launch_fill_int(count, 0, (size_t)n, s);
-    if (nnz > 0)
-        hipLaunchKernelGGL(k_histogram, dim3(grid_for(nnz, kBlock, 65536)), dim3(kBlock), 0, s,
-                           col_idx, nnz, count);
     launch_scan_int(count, n, col_ptr, bsum, s);
     launch_fill_int(count, 0, (size_t)n, s);
-    if (m > 0)
-        hipLaunchKernelGGL(k_scatter, dim3(grid_for(m, kBlock, 65536)), dim3(kBlock), 0, s,
-                           row_ptr, col_idx, m, col_ptr, count, row_idx);
+    if (nnz > 0)
+        hipLaunchKernelGGL(k_scatter, dim3((unsigned)((nnz + kEntries - 1) / kEntries)), dim3(kBlock), 0, s,
+                           row_ptr, col_idx, m, nnz, col_ptr, count, row_idx);
     if (n > 0)
         hipLaunchKernelGGL(k_sort_columns, dim3(grid_for(n, kBlock, 65536)), dim3(kBlock), 0, s,
-                           col_ptr, n, row_idx);
+                           col_ptr, n, row_idx, hi, ctl);
 }
 
-void launch_check_routes(const int *col_ptr, int n, double hi, Ctl *ctl, hipStream_t s)
+void launch_lengths(const int *ptr, int count, uint8_t *out, hipStream_t s)
 {
-    if (n == 0) return;
-    hipLaunchKernelGGL(k_check_routes, dim3(grid_for(n, kBlock, 16384)), dim3(kBlock), 0, s,
-                       col_ptr, n, hi, ctl);
+    if (count > 0)
+        hipLaunchKernelGGL(k_lengths, dim3(grid_for(count, kBlock, 4096)), dim3(kBlock), 0, s, ptr, count, out);
+}
+
+void launch_sample(const int *ptr, int m, int step, int count, int *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_sample, dim3(grid_for(count, kBlock, 4096)), dim3(kBlock), 0, s, ptr, m, step, count, out);
 }
 
 void launch_ctl_init(Ctl *ctl, double rho, double eps_tol, double eps_rel, double mu,
-                     double gamma, int adapt_every, hipStream_t s)
+                     double gamma, int adapt_every, long long iter, hipStream_t s)
 {
     hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(1), 0, s, ctl, rho, eps_tol, eps_rel, mu, gamma,
-                       adapt_every);
+                       adapt_every, iter);
 }
 
 void launch_ctl_set_tolerances(Ctl *ctl, double eps_tol, double eps_rel, double mu, double gamma,

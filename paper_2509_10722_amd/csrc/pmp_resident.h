@@ -524,14 +524,13 @@ int resident_plan(int m, int n, int longest_link, int longest_route, size_t sz)
     return 0;
 }
 
+// More than 64 KiB of LDS has to be asked for (a call small instances save).
 template <typename T>
-hipError_t resident_configure()
+hipError_t resident_configure(const Dev<T> &d)
 {
-    hipError_t e = hipSuccess;
-    for (const void *f : {(const void *)k_resident<T, true>, (const void *)k_resident<T, false>})
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResLds);
-    return e;
+    if (resident_lds(d.m, d.n, d.resident, sizeof(T)) <= 64 * 1024) return hipSuccess;
+    return hipFuncSetAttribute(d.resident == 1 ? (const void *)k_resident<T, true> : (const void *)k_resident<T, false>,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResLds);
 }
 
 template <typename T>
@@ -546,8 +545,8 @@ void launch_resident(const Dev<T> &d, long long iters, int ce, int adapt, hipStr
                            adapt);
 }
 
-template hipError_t resident_configure<float>();
-template hipError_t resident_configure<double>();
+template hipError_t resident_configure<float>(const Dev<float> &);
+template hipError_t resident_configure<double>(const Dev<double> &);
 template void launch_resident<float>(const Dev<float> &, long long, int, int, hipStream_t);
 template void launch_resident<double>(const Dev<double> &, long long, int, int, hipStream_t);
 

@@ -328,7 +328,7 @@ __global__ __launch_bounds__(kST) void k_staged_sort(StagedSide sd, const int *p
                                                      uint16_t *perm, uint4 *desc, int *total, int *fail)
 {
     __shared__ int hist[256];
-    __shared__ unsigned char width[kStK * kSW];
+    __shared__ unsigned char width[kStK * kSW], words[kStK * kST];
     const int c = blockIdx.x % sd.C, r = blockIdx.x / sd.C;
     const int r0 = r * sd.RB, nr = min(sd.RB, rows - r0), tid = threadIdx.x;
     const size_t t = (size_t)blockIdx.x;
@@ -337,14 +337,12 @@ __global__ __launch_bounds__(kST) void k_staged_sort(StagedSide sd, const int *p
     for (int i = tid; i < kStK * kSW; i += kST) width[i] = 0;
     for (int i = tid; i < kStK * kST; i += kST) out[i] = 0xffff;
     __syncthreads();
-    auto words = [&](int i) {
+    for (int i = tid; i < nr; i += kST) {
         int p, q;
         chunk_range(idx, ptr[r0 + i], ptr[r0 + i + 1], (long long)c * sd.CH, (long long)(c + 1) * sd.CH, p, q);
-        return (q - p + 1) / 2;
-    };
-    for (int i = tid; i < nr; i += kST) {
-        const int w = words(i);
-        if (w > 0) atomicAdd(&hist[255 - min(w, 255)], 1);
+        const int w = min((q - p + 1) / 2, 255);          // (255 is refused below)
+        words[i] = (unsigned char)w;
+        if (w > 0) atomicAdd(&hist[255 - w], 1);
     }
     __syncthreads();
     if (tid == 0) {
@@ -357,7 +355,7 @@ __global__ __launch_bounds__(kST) void k_staged_sort(StagedSide sd, const int *p
     }
     __syncthreads();
     for (int i = tid; i < nr; i += kST) {
-        const int w = min(words(i), 255);
+        const int w = words[i];
         if (w == 0) continue;
         const int at = atomicAdd(&hist[255 - w], 1), sl = at / 64, k = sl / kSW;
         const int wave = k & 1 ? kSW - 1 - sl % kSW : sl % kSW;
@@ -478,33 +476,40 @@ size_t staged_slots(const StagedSide &sd) { return (size_t)sd.R * sd.C * kStK * 
 size_t staged_words_cap(long long nnz) { return 2 * (size_t)nnz + 65536; }
 size_t staged_scratch_ints(const StagedSide &sd)
 {
-    return 2 * staged_tiles(sd) + 1 + scan_scratch_ints((int)staged_tiles(sd));
+    return 2 * staged_tiles(sd) + 2 + scan_scratch_ints((int)staged_tiles(sd));
 }
 
-// Builds one side's tables from its pointers and indices (CSC for streams, CSR
-// for links); scratch holds staged_scratch_ints ints and one more for the
-// failure flag.  *ok = false where the pattern is too uneven for them.
-hipError_t staged_build(StagedSide &sd, const int *ptr, const int *idx, int rows, long long nnz, uint16_t *perm,
-                        uint4 *desc, unsigned *words, int *scratch, bool *ok, hipStream_t s)
+hipError_t staged_build(StagedSide &ss, const StagedTables &ts, StagedSide &sl, const StagedTables &tl, long long nnz,
+                        int *scratch, bool *ok, hipStream_t s)
 {
-    const int tiles = (int)staged_tiles(sd);
-    int *total = scratch, *start = total + tiles, *bsum = start + tiles + 1;
-    int *fail = bsum + scan_scratch_ints(tiles);
-    launch_fill_int(fail, 0, 1, s);
-    hipLaunchKernelGGL(k_staged_sort, dim3(sd.R * sd.C), dim3(kST), 0, s, sd, ptr, idx, rows, perm, desc, total,
-                       fail);
-    launch_scan_int(total, tiles, start, bsum, s);
-    int h[2] = {0, 0};
-    hipError_t e = hipMemcpyAsync(&h[0], start + tiles, 4, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&h[1], fail, 4, hipMemcpyDeviceToHost, s);
+    StagedSide *sd[2] = {&ss, &sl};
+    const StagedTables *tb[2] = {&ts, &tl};
+    int *start[2], *fail[2], h[2][2] = {};
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < 2; ++k) {
+        const int tiles = (int)staged_tiles(*sd[k]);
+        int *total = scratch, *bsum = total + 2 * tiles + 2;
+        start[k] = total + tiles;
+        fail[k] = total + 2 * tiles + 1;                  // right behind the last start
+        scratch += staged_scratch_ints(*sd[k]);
+        launch_fill_int(fail[k], 0, 1, s);
+        hipLaunchKernelGGL(k_staged_sort, dim3(sd[k]->R * sd[k]->C), dim3(kST), 0, s, *sd[k], tb[k]->ptr, tb[k]->idx,
+                           tb[k]->rows, tb[k]->perm, tb[k]->desc, total, fail[k]);
+        launch_scan_int(total, tiles, start[k], bsum, s);
+        if (e == hipSuccess) e = hipMemcpyAsync(h[k], start[k] + tiles, 8, hipMemcpyDeviceToHost, s);
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
-    *ok = h[1] == 0 && h[0] >= 0 && (size_t)h[0] * 64 <= staged_words_cap(nnz);
+    *ok = true;
+    for (int k = 0; k < 2; ++k) *ok = *ok && h[k][1] == 0 && h[k][0] >= 0 && (size_t)h[k][0] * 64 <= staged_words_cap(nnz);
     if (!*ok) return hipSuccess;
-    hipLaunchKernelGGL(k_staged_fill, dim3(sd.R * sd.C), dim3(kST), 0, s, sd, ptr, idx, perm, desc, start, words);
-    sd.perm = perm;
-    sd.desc = desc;
-    sd.idx = words;
+    for (int k = 0; k < 2; ++k) {
+        hipLaunchKernelGGL(k_staged_fill, dim3(sd[k]->R * sd[k]->C), dim3(kST), 0, s, *sd[k], tb[k]->ptr, tb[k]->idx,
+                           tb[k]->perm, tb[k]->desc, start[k], tb[k]->words);
+        sd[k]->perm = tb[k]->perm;
+        sd[k]->desc = tb[k]->desc;
+        sd[k]->idx = tb[k]->words;
+    }
     return hipGetLastError();
 }
 
