@@ -27,13 +27,16 @@ void split_by_count(int count, int groups, int &blocks, int &size)
 // Blocks of both sides.  A side with fewer than 512 blocks (one workgroup
 // per CU) gets twice as many when the tiles keep at least 64 nonzeros on
 // average, so that two workgroups share each CU: measured on MI355X, +9% to
-// +13% at 2.5e7 to 6e7 nonzeros, while at 5e6 nonzeros the smaller tiles
-// cost more than the second workgroup gains.
+// +13% at 2.5e7 to 6e7 nonzeros.  Where both sides have 256 blocks, both
+// passes run their one-workgroup form (pmp_binned.hip), which is the faster up
+// to about 1.3e7 nonzeros (an iteration at 9e6: 51.8 us against 57.8, at
+// 1.2e7: 61.0 against 67.6, at 1.5e7: 87.9 against 86.7).
 void count_blocks(int m, int n, long long nnz, int &p0, int &lb0, int &q0, int &sb0)
 {
     split_by_count(m, 1, p0, lb0);
     split_by_count(n, 1, q0, sb0);
-    if (p0 < 512 && m >= 512 && nnz >= 64LL * 2 * p0 * q0) split_by_count(m, 2, p0, lb0);
+    const long long tile = p0 < 512 && q0 < 512 ? 200 : 64 * 2;
+    if (p0 < 512 && m >= 512 && nnz >= tile * p0 * q0) split_by_count(m, 2, p0, lb0);
     if (q0 < 512 && n >= 512 && nnz >= 64LL * p0 * 2 * q0) split_by_count(n, 2, q0, sb0);
 }
 

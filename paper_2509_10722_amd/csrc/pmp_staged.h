@@ -443,11 +443,12 @@ bool staged_plan(int m, int n, long long nnz, size_t sz, StagedSide &ss, StagedS
     // Times of an iteration in us, fitted to MI355X runs.  A chunk costs its
     // bytes at 62 KB/us (load path, then LDS writes) and 0.8 for the two
     // barriers and the sums between them.  Measured, against the layout taken
-    // otherwise: 1e5 links x 5e5 streams, nnz = 5e6: 30.8 against 43.1 binned
-    // (FP32), 43.9 against 64.2 gathered (FP64); 2e4 x 3e5, nnz = 2.4e6: 18 and
-    // 22 against 32 and 36; 1e5 x 1e6 in FP64: 56 against 119.  On the other
-    // side of the line: 2e5 x 5e5: 51 against 43 binned, 75 against 65
-    // gathered; 1e5 x 1e5, nnz = 8e5: 21 against 16 gathered.
+    // otherwise: 1e5 links x 5e5 streams, nnz = 5e6: 29.8 against 36.3 binned
+    // (FP32), 43.9 against 64.2 gathered (FP64); 1e5 x 1e6, nnz = 7.5e6: 39.3
+    // against 44.6 binned; 2e4 x 3e5, nnz = 2.4e6: 18 and 22 against 24 and 36;
+    // 1e5 x 1e6 in FP64: 56 against 119.  On the other side of the line: 2e5 x
+    // 5e5: 51 against 36.5 binned, 75 against 65 gathered; 1e5 x 3e5, nnz = 3e6:
+    // 25.6 against 25.0 binned; 1e5 x 1e5, nnz = 8e5: 21 against 16 gathered.
     const double mil = nnz * 1e-6;
     auto chunks = [&](const StagedSide &sd) { return sd.CPS * (0.8 + (double)sd.CH * sz / 62e3); };
     double best = 1e30;
@@ -467,7 +468,8 @@ bool staged_plan(int m, int n, long long nnz, size_t sz, StagedSide &ss, StagedS
     auto gather = [&](double bytes) {
         return 4.5 + mil * (bytes > 4.2e6 ? 9.0 : sz == 8 ? 4.9 : 4.1);
     };
-    const double other = binned ? 2 * (6.0 + 2.95 * mil) : gather((double)m * sz) + gather((double)n * sz);
+    auto messages = [&]() { return mil < 4.19 ? 13.7 + 3.7 * mil : mil < 13.1 ? 20.0 + 3.3 * mil : 12.0 + 5.9 * mil; };
+    const double other = binned ? messages() : gather((double)m * sz) + gather((double)n * sz);
     return staged < 0.95 * other;
 }
 
