@@ -39,7 +39,7 @@ def _instance(m, n, lo, hi, long_streams=0, hot_links=0, seed=6):
 
 
 CASES = [
-    (40000, 1023, 2, 5, 3, 0),          # a stream block of 40000 entries: past the groups and the kept indices
+    (15800, 1023, 2, 5, 4, 0),          # a stream block of 21000 entries: past the groups and the kept indices
     (3000, 30011, 1, 3, 0, 2),          # long links alone in their blocks
     (1100000, 20000, 3, 6, 0, 0),       # more than four rows a lane on the link side
     (20000, 540000, 1, 2, 0, 0),        # more than two on the stream side
