@@ -48,20 +48,27 @@ constexpr int kBT = 2 * kBlock;
 // nonzero tiles: 1.80 s).
 constexpr int kBS = 2 * kCap;
 
-// Grid barrier in two levels.  Blocks are dealt to the 8 XCDs in turn, so
-// the blocks with one value of blockIdx.x mod 8 (one XCD) first meet on their
-// group's counter; the last of each group arrives at the top counter, and the
-// last of those advances the generation that the others wait on.  Every
-// counter and flag sits on a 256-byte line of its own (waiting blocks poll
-// the generation while others add to the counters).  Each block makes its
-// writes visible with one release fence before it arrives and takes the
-// others' with one acquire fence after the wait (each an L2 writeback or
-// invalidate on this GPU); the last arrivals of a group and of the top pass
-// the writes they have taken on with an acquire-release fence.  Measured with
-// 512 workgroups: about 9.5 us a barrier, against 26 us for one counter
-// shared with the generation word and sequentially consistent fences on both
-// sides.
+// Grid barrier in two levels: the blocks of one XCD meet on their group's
+// counter; the last of each group arrives at the top counter, and the last of
+// those advances the generation that the others wait on.  Every counter and
+// flag sits on a 256-byte line of its own (waiting blocks poll the generation
+// while others add to the counters).
+//
+// An XCD's workgroups share its L2, so a block only waits until its stores
+// are there; the last arrival of a group writes that L2 back for all of them
+// (one agent-scope release an XCD), and each block takes the others' writes
+// with one acquire fence after the wait.  With a release in every block the
+// early arrivals wrote the L2 back over and over under the blocks still at
+// work: 16 instances of 1,000 to 100,000 links, an iteration 99.5 us with
+// barriers of 19.5 and 16.1 and tiles of 33.2 and 28.0, against 76.3 with 12.2,
+// 9.8, 28.1 and 23.9 (FP64 108.0 -> 79.7).
+//
+// The groups are counted by the XCDs the blocks run on (hardware register), in
+// a first barrier that takes blockIdx.x mod 8 for the group (blocks are dealt
+// to the 8 XCDs in turn, but nothing here relies on it) and in which every block
+// releases for itself.
 constexpr int kBarTop = 0, kBarGen = 64, kBarAbort = 128, kBarGroup = 192;
+constexpr int kBarCensus = 32;                  // in a group's line: its blocks
 constexpr int kBarWords = kBarGroup + 64 * 8;   // unsigned words of BDev::bar
 
 // Blocks of barrier group x (blockIdx.x mod 8 == x) in a grid of nblocks,
@@ -75,24 +82,28 @@ __host__ __device__ __forceinline__ unsigned barrier_groups(unsigned nblocks)
     return nblocks < 8 ? nblocks : 8u;
 }
 
-__device__ bool grid_sync(unsigned *bar, int *abort, unsigned nblocks, unsigned long long spin_limit)
+// A block's group, its blocks and the number of groups; one_xcd: they share an L2.
+struct BarGroup {
+    unsigned x, size, groups;
+    bool one_xcd;
+};
+
+__device__ bool grid_sync(unsigned *bar, int *abort, const BarGroup &bg, unsigned long long spin_limit)
 {
     __shared__ int s_ok;
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's stores are in L2
     __syncthreads();
     if (threadIdx.x == 0) {
         int ok = 1;
         unsigned *top = bar + kBarTop, *genp = bar + kBarGen;
-        const unsigned x = blockIdx.x % 8;
-        unsigned *grp = bar + kBarGroup + 64 * x;
-        const unsigned gsize = barrier_group_size(x, nblocks);
-        const unsigned groups = barrier_groups(nblocks);
+        unsigned *grp = bar + kBarGroup + 64 * bg.x;
         const unsigned gen = __hip_atomic_load(genp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        if (!bg.one_xcd) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         bool last = false;
-        if (atomicAdd(grp, 1u) == gsize - 1) {
+        if (atomicAdd(grp, 1u) == bg.size - 1) {
             __hip_atomic_store(grp, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
-            if (atomicAdd(top, 1u) == groups - 1) {
+            if (atomicAdd(top, 1u) == bg.groups - 1) {
                 __hip_atomic_store(top, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
                 __hip_atomic_fetch_add(genp, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -440,7 +451,18 @@ __global__ __launch_bounds__(kBT) void k_batch(BDev<T> d, int max_iter, int ce, 
         d.ictl[i].done = 0;
     for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < d.nlt; t += G * blockDim.x)
         d.lt_hcnt[t] = 0;
-    if (!grid_sync(d.bar, d.abort, G, d.spin_limit)) return;
+    const unsigned xcd = (unsigned)xcc_id() % 8u;
+    if (threadIdx.x == 0) atomicAdd(d.bar + kBarGroup + 64 * xcd + kBarCensus, 1u);
+    const unsigned bx = blockIdx.x % 8u;
+    if (!grid_sync(d.bar, d.abort, BarGroup{bx, barrier_group_size(bx, G), barrier_groups(G), false}, d.spin_limit))
+        return;
+    BarGroup bg{xcd, 0, 0, true};
+    for (unsigned x = 0; x < 8; ++x) {
+        const unsigned blocks = __hip_atomic_load(d.bar + kBarGroup + 64 * x + kBarCensus, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+        if (x == xcd) bg.size = blocks;
+        bg.groups += blocks > 0;
+    }
     long long last_check = 0;
     for (int it = 1; it <= max_iter; ++it) {
         const bool check = it % ce == 0 || it == max_iter;
@@ -451,7 +473,7 @@ __global__ __launch_bounds__(kBT) void k_batch(BDev<T> d, int max_iter, int ce, 
             else stream_tile<T, false>(d, r.t, sv, sred);
         }
         lap(0);
-        if (!grid_sync(d.bar, d.abort, G, d.spin_limit)) return;
+        if (!grid_sync(d.bar, d.abort, bg, d.spin_limit)) return;
         lap(1);
         for (TileRange r = xcd_tiles(d.nlt, G); r.t < r.end; r.t += r.step) {
             if (check) link_tile<T, kCheck>(d, r.t, sv, sred);
@@ -459,7 +481,7 @@ __global__ __launch_bounds__(kBT) void k_batch(BDev<T> d, int max_iter, int ce, 
             else link_tile<T, kPlain>(d, r.t, sv, sred);
         }
         lap(2);
-        if (!grid_sync(d.bar, d.abort, G, d.spin_limit)) return;
+        if (!grid_sync(d.bar, d.abort, bg, d.spin_limit)) return;
         lap(3);
         if (!check) continue;
         // finalize: one workgroup per instance, partials in tile order
@@ -482,7 +504,7 @@ __global__ __launch_bounds__(kBT) void k_batch(BDev<T> d, int max_iter, int ce, 
                          ss + sl);
             __syncthreads();
         }
-        if (!grid_sync(d.bar, d.abort, G, d.spin_limit)) return;
+        if (!grid_sync(d.bar, d.abort, bg, d.spin_limit)) return;
         lap(4);
         int active = 0;
         bool rescale = false;
@@ -502,7 +524,7 @@ __global__ __launch_bounds__(kBT) void k_batch(BDev<T> d, int max_iter, int ce, 
                     d.g.u[l] = ut;
                 }
             }
-            if (!grid_sync(d.bar, d.abort, G, d.spin_limit)) return;
+            if (!grid_sync(d.bar, d.abort, bg, d.spin_limit)) return;
         }
     }
     lap(5);

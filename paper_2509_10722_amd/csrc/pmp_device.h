@@ -11,6 +11,12 @@ namespace pmp {
 
 __device__ __forceinline__ int ld_stream(const int *p) { return __builtin_nontemporal_load(p); }
 
+// The XCD this wave runs on.
+__device__ __forceinline__ int xcc_id()
+{
+    return __builtin_amdgcn_s_getreg(20 | (3 << 11));   // HW_REG_XCC_ID, 4 bits
+}
+
 __device__ __forceinline__ double wave_sum(double v)
 {
 #pragma unroll

@@ -55,11 +55,6 @@ constexpr unsigned long long kRollTicks = 400000;    // 4 ms of the 100 MHz wall
 constexpr unsigned kResPolls = 1u << 26;             // bound of a phase barrier's wait
 constexpr unsigned kOpen = 0, kSolo = 99;            // ResSync::win: nobody yet / no group
 
-__device__ __forceinline__ int xcc_id()
-{
-    return __builtin_amdgcn_s_getreg(20 | (3 << 11));   // HW_REG_XCC_ID, 4 bits
-}
-
 template <typename V>
 __device__ __forceinline__ V ld_agent(const V *p)
 {
