@@ -121,7 +121,10 @@ typedef struct {
  *                nonzero per direction, streamed through HBM in coalesced
  *                runs (for large unstructured R, where random gathers are
  *                slow); with FP32 its sums equal the gather layout's bit for
- *                bit whenever they are exact in FP64. */
+ *                bit whenever they are exact in FP64.  Under AUTO, instances
+ *                whose vectors are small enough run passes that gather from
+ *                LDS in place of either; under AUTO and GATHER, instances
+ *                that fit on chip run their iterations in one launch. */
 typedef enum { PMP_LAYOUT_AUTO = 0, PMP_LAYOUT_GATHER = 1, PMP_LAYOUT_BINNED = 2 } pmp_layout;
 typedef struct {
     double rho0, alpha, mu, gamma, eps_abs;
