@@ -91,7 +91,9 @@ struct BarGroup {
 __device__ bool grid_sync(unsigned *bar, int *abort, const BarGroup &bg, unsigned long long spin_limit)
 {
     __shared__ int s_ok;
-    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's stores are in L2
+    // no store moves below the fence, and vmcnt(0) after it: this wave's are in L2
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0x0f70);
     __syncthreads();
     if (threadIdx.x == 0) {
         int ok = 1;
