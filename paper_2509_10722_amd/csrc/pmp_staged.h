@@ -302,28 +302,31 @@ __global__ void k_staged_adj_cast(const double *y, int m, T *yt)
 
 // ---- tables ------------------------------------------------------------------
 
-// First and last + 1 entry of row [b, e) (column indices ascending) in
-// [lo, hi).
+// First entry of [b, e) whose index is not below v (indices ascending).  Entry
+// numbers go up to 2^31 - 1, so the middle is formed from the distance.
+template <typename I>
+__host__ __device__ __forceinline__ int lower_entry(const I &idx, int b, int e, long long v)
+{
+    while (b < e) {
+        const int mid = b + (e - b) / 2;
+        if (idx[mid] < v) b = mid + 1;
+        else e = mid;
+    }
+    return b;
+}
+
+// First and last + 1 entry of row [b, e) in [lo, hi).
 __device__ __forceinline__ void chunk_range(const int *idx, int b, int e, long long lo, long long hi, int &p,
                                             int &q)
 {
-    auto lower = [&](long long v) {
-        int x = b, y = e;
-        while (x < y) {
-            const int mid = (x + y) / 2;
-            if (idx[mid] < v) x = mid + 1;
-            else y = mid;
-        }
-        return x;
-    };
-    p = lower(lo);
-    q = lower(hi);
+    p = lower_entry(idx, b, e, lo);
+    q = lower_entry(idx, b, e, hi);
 }
 
 // Tile (r, c): its rows sorted by their words there, most first, in slots
-// (slice k of a wave: the slices go round the waves forth and back), the
-// every wave's words and the mask of those that end a slice.  A wave of more
-// than 64 words sets *fail.
+// (slice k of a wave: the slices go round the waves forth and back), every
+// wave's words and the mask of those that end a slice.  A wave of more than 64
+// words sets *fail.
 __global__ __launch_bounds__(kST) void k_staged_sort(StagedSide sd, const int *ptr, const int *idx, int rows,
                                                      uint16_t *perm, uint4 *desc, int *total, int *fail)
 {
@@ -432,6 +435,15 @@ bool staged_side(int rows, int src, size_t sz, int S, StagedSide &sd)
     return true;
 }
 
+// A wave holds at most 64 words of two entries a lane in a chunk, so a tile at
+// most 128 entries a lane and a row at most 128.  Above that on average some
+// wave is too full for certain: such tables are not begun (their set-up walks
+// every row of every tile).
+bool staged_room(const StagedSide &sd, int rows, long long nnz)
+{
+    return nnz <= 128LL * sd.C * std::min<long long>(rows, (long long)sd.R * kST);
+}
+
 size_t staged_lds(const StagedSide &sd, size_t sz) { return (size_t)sd.RB * 8 + ((size_t)sd.CH + 8) * sz; }
 
 }  // namespace
@@ -443,7 +455,7 @@ bool staged_plan(int m, int n, long long nnz, size_t sz, StagedSide &ss, StagedS
     // launches, not three: 1e4 links x 1e5 streams, nnz = 7.5e5, an iteration
     // 14.1 us against 16.1 (FP64), 12.8 against 13.0 (FP32).
     if (small_blocks(nnz)) return false;
-    if (!staged_side(n, m, sz, 1, ss) || ss.R > kSmallBlocks) return false;
+    if (!staged_side(n, m, sz, 1, ss) || ss.R > kSmallBlocks || !staged_room(ss, n, nnz)) return false;
     // Times of an iteration in us, fitted to MI355X runs.  A chunk costs its
     // bytes at 62 KB/us (load path, then LDS writes) and 0.8 for the two
     // barriers and the sums between them.  Measured, against the layout taken
@@ -465,7 +477,7 @@ bool staged_plan(int m, int n, long long nnz, size_t sz, StagedSide &ss, StagedS
             sl = t;
         }
     }
-    if (best > 1e29) return false;
+    if (best > 1e29 || !staged_room(sl, m, nnz)) return false;
     const double staged = 3.5 + chunks(ss) + 3.0 + best + 4.5 + 0.5 * mil;
     // the other layouts: gathers from L2 (or past it), binned messages
     const bool binned = sz == 4 && nnz >= (1LL << 21);

@@ -1,0 +1,82 @@
+// Index arithmetic and planning rules of the HIP library at sizes that no test
+// runs on a GPU, under AddressSanitizer and UndefinedBehaviorSanitizer (host
+// code only; no GPU call is made).  The translation unit includes the source
+// whose helpers have internal linkage; the other sources are linked as usual.
+#include "pmp_kernels.hip"
+
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+
+using namespace pmp;
+
+#define REQUIRE(cond)                                                          \
+    do {                                                                       \
+        if (!(cond)) {                                                         \
+            std::fprintf(stderr, "%s:%d: check failed: %s\n", __FILE__, __LINE__, #cond); \
+            std::exit(1);                                                      \
+        }                                                                      \
+    } while (0)
+
+// Entries [b, e) of a pattern of up to 2^31 - 1 nonzeros without their memory:
+// entry k holds 3 (k - b); a read outside the row ends the program.
+struct RowOf {
+    int b, e;
+    int operator[](int k) const
+    {
+        REQUIRE(k >= b && k < e);
+        return 3 * (k - b);
+    }
+};
+
+static void check_lower_entry()
+{
+    const int rows[][2] = {{0, 0},
+                           {0, 1},
+                           {5, 4000},
+                           {(1 << 30) - 7, (1 << 30) + 9},
+                           {1079990000, 1080000000},
+                           {2147483647 - 5000, 2147483647}};
+    for (auto &r : rows) {
+        const RowOf row{r[0], r[1]};
+        for (long long v : {-1LL, 0LL, 1LL, 2999LL, 3000LL, 14997LL, 1LL << 31}) {
+            const long long k = r[0] + (v <= 0 ? 0 : (v + 2) / 3);
+            REQUIRE(lower_entry(row, r[0], r[1], v) == (int)std::min<long long>(k, r[1]));
+        }
+    }
+}
+
+// Tables that a pattern of these sizes cannot fit are not planned; the shapes
+// that run staged still are.
+static void check_staged_plan()
+{
+    StagedSide ss, sl;
+    for (size_t sz : {(size_t)4, (size_t)8}) {
+        REQUIRE(!staged_plan(300000, 1040000, 1080000000LL, sz, ss, sl));
+        REQUIRE(staged_plan(100000, 500000, 5000000LL, sz, ss, sl));
+        REQUIRE(staged_plan(20003, 200007, 1600000LL, sz, ss, sl));
+    }
+    const int sizes[][2] = {{5000, 150000}, {20000, 200000}, {100000, 1000000}, {300000, 1040000}, {2000000, 1040000}};
+    for (auto &z : sizes)
+        for (long long nnz = 1 << 20; nnz < (1LL << 31); nnz += nnz / 3)
+            for (size_t sz : {(size_t)4, (size_t)8}) {
+                if (!staged_plan(z[0], z[1], nnz, sz, ss, sl)) continue;
+                const StagedSide *side[2] = {&ss, &sl};
+                for (int k = 0; k < 2; ++k) {
+                    const StagedSide &sd = *side[k];
+                    const int rows = k ? z[0] : z[1];
+                    // a tile's mean is within what its 16 waves hold
+                    REQUIRE(nnz / ((long long)sd.R * sd.C) <= 16LL * 64 * 64 * 2);
+                    REQUIRE(nnz / ((long long)rows * sd.C) <= 128);
+                    REQUIRE(sd.C <= 32 * 63 && (long long)sd.CH * sd.C >= sd.src);
+                }
+            }
+}
+
+int main()
+{
+    check_lower_entry();
+    check_staged_plan();
+    std::printf("host entries: all checks passed\n");
+    return 0;
+}
