@@ -436,8 +436,9 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
             for (int l = 0; l < m; ++l) {
                 const int b = hrow[(size_t)l], e = hrow[(size_t)l + 1];
                 if (e - b <= kCap || (e - b > kLongChunk) != (pass == 0)) continue;
-                for (int k = b; k < e; k += kLongChunk)
-                    ck.push_back(make_int4(k, std::min(e, k + kLongChunk), pass ? l : -1, (int)lr.size()));
+                for_chunks(b, e, [&](int k, int next) {
+                    ck.push_back(make_int4(k, next, pass ? l : -1, (int)lr.size()));
+                });
                 lr.push_back(l);
                 if (!pass) lck.push_back((int)ck.size());
             }

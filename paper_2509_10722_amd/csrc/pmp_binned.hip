@@ -171,7 +171,7 @@ __device__ __forceinline__ void accumulate(const T *__restrict__ msg,
         const int lane = threadIdx.x & 63;
         // every lane of a wave takes the same trips (the run merge is
         // wave-wide); a lane past the end loads nothing
-        const int b1 = (e1 + 3) >> 2;
+        const int b1 = quads_end(e1);
         for (int bw = (e0 >> 2) + (threadIdx.x & ~63); bw < b1; bw += kBinThreads) {
             const int b = bw + lane;
             const bool in = b < b1;
@@ -461,7 +461,7 @@ struct OneEntries {
     __device__ __forceinline__ void load(const T *msg, const uint16_t *idx, int e0, int e1)
     {
         constexpr int kNt = 2;                             // non-temporal
-        const int q0 = e0 >> 2, nq = min(((e1 + 3) >> 2) - q0, K * kBinThreads);
+        const int q0 = e0 >> 2, nq = min(quads_end(e1) - q0, K * kBinThreads);
         auto m = __builtin_amdgcn_make_buffer_rsrc((void *)((const v4 *)msg + q0), 0, nq * (int)sizeof(v4), kRawBuffer);
         auto x = __builtin_amdgcn_make_buffer_rsrc((void *)((const u4 *)idx + q0), 0, nq * (int)sizeof(u4), kRawBuffer);
 #pragma unroll
@@ -480,7 +480,7 @@ struct OneEntries {
     __device__ __forceinline__ void add(const T *msg, const uint16_t *idx, int e0, int e1, acc_t *acc, u4 *cache,
                                         double fxs)
     {
-        const int lane = threadIdx.x & 63, q0 = e0 >> 2, b1 = (e1 + 3) >> 2;
+        const int lane = threadIdx.x & 63, q0 = e0 >> 2, b1 = quads_end(e1);
         int w = q0 + (threadIdx.x & ~63);
 #pragma unroll
         for (int g = 0; g < K; ++g, w += kBinThreads)
@@ -618,7 +618,7 @@ PMP_BIN_ONE_KERNEL void k_bin_stream_one(Dev<T> d, int cap, int nt)
         return;
     }
     uint16_t *kept = (uint16_t *)(S + d.SB);
-    const bool fits = ((e1 + 3) & ~3) - (e0 & ~3) <= cap;
+    const bool fits = quads_end(e1) - (e0 >> 2) <= cap / 4;
     constexpr int G = kOneStreams;
     OneEntries<T, false, false> en;
     OneStreams<T, MODE, G> rows;
@@ -679,7 +679,7 @@ PMP_BIN_ONE_KERNEL void k_bin_link_one(Dev<T> d, int cap, int nt)
         return;
     }
     uint16_t *kept = (uint16_t *)(Y + d.LB);
-    const bool fits = ((e1 + 3) & ~3) - (e0 & ~3) <= cap;
+    const bool fits = quads_end(e1) - (e0 >> 2) <= cap / 4;
     constexpr int G = MODE == kCheck || sizeof(T) == 8 ? 2 : kOneLinks;   // a check carries more inputs
     OneEntries<T, sizeof(T) == 4 && PMP_BIN_RUNS, FX> en;
     OneLinks<T, MODE, G> rows;

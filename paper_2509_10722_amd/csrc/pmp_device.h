@@ -157,6 +157,20 @@ __device__ __forceinline__ double run_sum4(const T *sh, int b, int e, int sub)
     return s;
 }
 
+// Last + 1 group of four entries of a run that ends at entry e1 (up to 2^31 - 1).
+__host__ __device__ __forceinline__ int quads_end(int e1) { return (e1 >> 2) + ((e1 & 3) != 0); }
+
+// Entries of one lane of a workgroup that strides over cnt of them, in rounds
+// of eight: round(k) where k, k + kBlock, ... k + 7 kBlock are all there, then
+// last(k) for the rest.  Counts go up to 2^31 - 1; in unsigned no sum wraps.
+template <typename R, typename L>
+__host__ __device__ __forceinline__ void strided_rounds(unsigned cnt, unsigned lane, R round, L last)
+{
+    unsigned k = lane;
+    for (; k + 7u * kBlock < cnt; k += 8u * kBlock) round(k);
+    if (k < cnt) last(k);
+}
+
 // Sum of tab[idx[k]] over k = b + threadIdx.x, + kBlock, ... below e, added in
 // that order, in FP64 or (term: FP64 -> int64) in integers; eight gathers per
 // lane in flight.
@@ -165,28 +179,30 @@ __device__ __forceinline__ A strided_sum(const int *__restrict__ idx, const T *t
                                          F term)
 {
     A acc = 0;
-    int k = b + (int)threadIdx.x;
-    for (; k + 7 * kBlock < e; k += 8 * kBlock) {
+    const int *p = idx + b;
+    const unsigned cnt = (unsigned)(e - b);
+    auto round = [&](unsigned k) {
         int id[8];
         T v[8];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) id[r] = ld_stream(idx + k + r * kBlock);
+        for (int r = 0; r < 8; ++r) id[r] = ld_stream(p + k + r * kBlock);
 #pragma unroll
         for (int r = 0; r < 8; ++r) v[r] = tab[id[r]];
 #pragma unroll
         for (int r = 0; r < 8; ++r) acc += term((double)v[r]);
-    }
-    if (k < e) {
+    };
+    auto last = [&](unsigned k) {
         int id[8];
         T v[8];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) id[r] = k + r * kBlock < e ? ld_stream(idx + k + r * kBlock) : -1;
+        for (int r = 0; r < 8; ++r) id[r] = k + r * kBlock < cnt ? ld_stream(p + k + r * kBlock) : -1;
 #pragma unroll
         for (int r = 0; r < 8; ++r) v[r] = id[r] >= 0 ? tab[id[r]] : T(0);
 #pragma unroll
         for (int r = 0; r < 8; ++r)
             if (id[r] >= 0) acc += term((double)v[r]);
-    }
+    };
+    strided_rounds(cnt, threadIdx.x, round, last);
     return acc;
 }
 

@@ -40,6 +40,16 @@ inline int block_nonzeros(long long nnz)
 // by several workgroups, one per chunk of kLongChunk nonzeros; a second
 // kernel adds the chunk sums in chunk order and runs the link update.
 constexpr int kLongChunk = 8192;
+// Chunks [k, k + length) of the entries [b, e) of a long row (e up to 2^31 - 1).
+template <typename F>
+void for_chunks(int b, int e, F chunk)
+{
+    for (int k = b; k < e;) {
+        const int next = k + std::min(e - k, kLongChunk);
+        chunk(k, next);
+        k = next;
+    }
+}
 // Shift F of the fixed-point long-row sums (Dev::fx_shift) of a problem with
 // element size `elem`, longest long row `maxlong` (0 if none) and box upper
 // bound `hi`: the largest F with maxlong x hi x 2^F <= 2^62 (so every term and

@@ -404,9 +404,9 @@ __global__ __launch_bounds__(kST) void k_staged_fill(StagedSide sd, const int *p
                             (long long)(c + 1) * sd.CH, p, q);
         }
         const unsigned lo = p < q ? (unsigned)(idx[p] - c * sd.CH) : (unsigned)sd.CH;
-        const unsigned hi = p + 1 < q ? (unsigned)(idx[p + 1] - c * sd.CH) : (unsigned)sd.CH;
+        const unsigned hi = q - p > 1 ? (unsigned)(idx[p + 1] - c * sd.CH) : (unsigned)sd.CH;
         out[(size_t)i * 64] = lo | hi << 16;
-        p = min(p + 2, q);
+        p += min(2, q - p);
     }
     if (lane == 0) desc[t * kSW + wave].x = at;
 }

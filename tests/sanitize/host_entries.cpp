@@ -73,8 +73,43 @@ static void check_staged_plan()
             }
 }
 
+// Walks over entries that end at 2^31 - 1: every entry once, nothing beyond.
+static void check_walks()
+{
+    const unsigned counts[] = {0u, 1u, 255u, 256u, 2047u, 2048u, 2049u, 5000u, 2147483647u - 1792u, 2147483647u};
+    for (unsigned cnt : counts)
+        for (unsigned lane : {0u, 1u, 254u, 255u}) {
+            unsigned next = lane;
+            bool ended = false;
+            strided_rounds(cnt, lane,
+                           [&](unsigned k) {
+                               REQUIRE(!ended && k == next && (unsigned long long)k + 7 * kBlock < cnt);
+                               next = k + 8 * kBlock;
+                           },
+                           [&](unsigned k) {
+                               REQUIRE(!ended && k == next && k < cnt);
+                               ended = true;
+                               for (int r = 0; r < 8; ++r) next = (unsigned long long)k + r * kBlock < cnt ? k + (r + 1) * kBlock : next;
+                           });
+            REQUIRE(next >= cnt && (lane >= cnt || next - cnt < (unsigned)kBlock));
+        }
+    const int rows[][2] = {{0, 4097}, {7, 7 + 8192}, {7, 7 + 8193}, {2147483647 - 50000, 2147483647}};
+    for (auto &r : rows) {
+        int at = r[0], chunks = 0;
+        for_chunks(r[0], r[1], [&](int b, int e) {
+            REQUIRE(b == at && e > b && e - b <= kLongChunk && e <= r[1]);
+            at = e;
+            ++chunks;
+        });
+        REQUIRE(at == r[1] && chunks == (r[1] - r[0] + kLongChunk - 1) / kLongChunk);
+    }
+    for (long long e : {0LL, 1LL, 3LL, 4LL, 5LL, 2147483644LL, 2147483645LL, 2147483647LL})
+        REQUIRE(quads_end((int)e) == (int)((e + 3) / 4));
+}
+
 int main()
 {
+    check_walks();
     check_lower_entry();
     check_staged_plan();
     std::printf("host entries: all checks passed\n");
