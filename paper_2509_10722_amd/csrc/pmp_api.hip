@@ -287,6 +287,59 @@ pmp_status check_shape(const pmp_problem *p)
     return PMP_OK;
 }
 
+// The gather passes' tables: their workgroups' blocks and the chunks of long
+// rows, made from the pointer arrays on the host.
+template <typename T>
+pmp_status gather_tables(Dev<T> &d, const Layout &L, bool long_rows, hipStream_t s)
+{
+    std::vector<int> hrow((size_t)d.m + 1), hcol((size_t)d.n + 1);
+    HIP_TRY(hipMemcpyAsync(hrow.data(), d.row_ptr, hrow.size() * 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(hcol.data(), d.col_ptr, hcol.size() * 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    auto blocks = [&](const std::vector<int> &ptr, int count) {
+        const std::vector<int> b = make_blocks(ptr, count, block_segments(count, d.nnz), block_nonzeros(d.nnz));
+        std::vector<int4> t;
+        t.reserve(b.size());
+        for (size_t i = 0; i + 1 < b.size(); ++i)
+            t.push_back(make_int4(b[i], b[i + 1], ptr[(size_t)b[i]], ptr[(size_t)b[i + 1]]));
+        return t;
+    };
+    std::vector<int4> sblk = blocks(hcol, d.n), lblk = blocks(hrow, d.m);
+    d.nsb = (int)sblk.size();
+    d.nlb = (int)lblk.size();
+    if (d.nsb > L.nsb_max || d.nlb > L.nlb_max)
+        return fail(PMP_ERR_SHAPE, "internal: block tables exceed their bound");
+    if (d.nsb) HIP_TRY(hipMemcpyAsync((void *)d.sblk, sblk.data(), sblk.size() * sizeof(int4), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync((void *)d.lblk, lblk.data(), lblk.size() * sizeof(int4), hipMemcpyHostToDevice, s));
+    // rows longer than kCap: chunks of kLongChunk nonzeros, the rows of
+    // several chunks first
+    std::vector<int4> ck;
+    std::vector<int> lr, lck{0};
+    for (int pass = 0; long_rows && pass < 2; ++pass) {
+        for (int l = 0; l < d.m; ++l) {
+            const int b = hrow[(size_t)l], e = hrow[(size_t)l + 1];
+            if (e - b <= kCap || (e - b > kLongChunk) != (pass == 0)) continue;
+            for_chunks(b, e, [&](int k, int next) {
+                ck.push_back(make_int4(k, next, pass ? l : -1, (int)lr.size()));
+            });
+            lr.push_back(l);
+            if (!pass) lck.push_back((int)ck.size());
+        }
+        if (!pass) d.nlm = (int)lr.size();
+    }
+    d.nlc = (int)ck.size();
+    d.nlr = (int)lr.size();
+    if (d.nlc > L.nlc_max || d.nlr > L.nlr_max)
+        return fail(PMP_ERR_SHAPE, "internal: long-row tables exceed their bound");
+    if (d.nlc) {
+        HIP_TRY(hipMemcpyAsync((void *)d.lck, ck.data(), ck.size() * sizeof(int4), hipMemcpyHostToDevice, s));
+        HIP_TRY(hipMemcpyAsync((void *)d.lr_row, lr.data(), lr.size() * 4, hipMemcpyHostToDevice, s));
+        HIP_TRY(hipMemcpyAsync((void *)d.lr_ck, lck.data(), lck.size() * 4, hipMemcpyHostToDevice, s));
+    }
+    HIP_TRY(hipStreamSynchronize(s));   // the host vectors go out of scope
+    return PMP_OK;
+}
+
 template <typename T>
 pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
 {
@@ -404,56 +457,20 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
         HIP_TRY(staged_build(d.ss, ts, d.sl, tl, nnz, (int *)(ws + L.st_scratch), &ok, s));
         if (ok) HIP_TRY(staged_configure<T>());
         d.staged = ok ? 1 : 0;
+        // The staged passes of reverse mode hold ybar and Sbar in the problem's
+        // precision, as the binned messages do.  FP32 problems that the binned
+        // layout would not take gather them in FP64 instead (their blocks:
+        // forward_ckpt_impl).  Gradient of 100 iterations at 20,003 links x
+        // 200,007 streams, nnz = 1.6e6: 6.1 ms, with FP32 vectors 5.3 ms and 2e-8
+        // off (gather passes throughout: 7.5 ms).
+        d.staged_adj = ok && (sizeof(T) == 8 || L.binned) ? 1 : 0;
     }
     d.binned = L.binned && !d.staged ? 1 : 0;
     // Only the gather passes need tables made from the pointer arrays on the
     // host (5e6 nonzeros: 2.5 ms for the copies and the loops over the rows).
     if (!d.staged && !d.binned) {
-        std::vector<int> hrow((size_t)m + 1), hcol((size_t)n + 1);
-        HIP_TRY(hipMemcpyAsync(hrow.data(), row_ptr, hrow.size() * 4, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(hcol.data(), col_ptr, hcol.size() * 4, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        auto blocks = [&](const std::vector<int> &ptr, int count) {
-            const std::vector<int> b = make_blocks(ptr, count, block_segments(count, nnz), block_nonzeros(nnz));
-            std::vector<int4> t;
-            t.reserve(b.size());
-            for (size_t i = 0; i + 1 < b.size(); ++i)
-                t.push_back(make_int4(b[i], b[i + 1], ptr[(size_t)b[i]], ptr[(size_t)b[i + 1]]));
-            return t;
-        };
-        std::vector<int4> sblk = blocks(hcol, n), lblk = blocks(hrow, m);
-        d.nsb = (int)sblk.size();
-        d.nlb = (int)lblk.size();
-        if (d.nsb > L.nsb_max || d.nlb > L.nlb_max)
-            return fail(PMP_ERR_SHAPE, "internal: block tables exceed their bound");
-        if (d.nsb) HIP_TRY(hipMemcpyAsync((void *)d.sblk, sblk.data(), sblk.size() * sizeof(int4), hipMemcpyHostToDevice, s));
-        HIP_TRY(hipMemcpyAsync((void *)d.lblk, lblk.data(), lblk.size() * sizeof(int4), hipMemcpyHostToDevice, s));
-        // rows longer than kCap: chunks of kLongChunk nonzeros, the rows of
-        // several chunks first
-        std::vector<int4> ck;
-        std::vector<int> lr, lck{0};
-        for (int pass = 0; long_rows && pass < 2; ++pass) {
-            for (int l = 0; l < m; ++l) {
-                const int b = hrow[(size_t)l], e = hrow[(size_t)l + 1];
-                if (e - b <= kCap || (e - b > kLongChunk) != (pass == 0)) continue;
-                for_chunks(b, e, [&](int k, int next) {
-                    ck.push_back(make_int4(k, next, pass ? l : -1, (int)lr.size()));
-                });
-                lr.push_back(l);
-                if (!pass) lck.push_back((int)ck.size());
-            }
-            if (!pass) d.nlm = (int)lr.size();
-        }
-        d.nlc = (int)ck.size();
-        d.nlr = (int)lr.size();
-        if (d.nlc > L.nlc_max || d.nlr > L.nlr_max)
-            return fail(PMP_ERR_SHAPE, "internal: long-row tables exceed their bound");
-        if (d.nlc) {
-            HIP_TRY(hipMemcpyAsync((void *)d.lck, ck.data(), ck.size() * sizeof(int4), hipMemcpyHostToDevice, s));
-            HIP_TRY(hipMemcpyAsync((void *)d.lr_row, lr.data(), lr.size() * 4, hipMemcpyHostToDevice, s));
-            HIP_TRY(hipMemcpyAsync((void *)d.lr_ck, lck.data(), lck.size() * 4, hipMemcpyHostToDevice, s));
-        }
-        HIP_TRY(hipStreamSynchronize(s));   // the host vectors go out of scope
+        const pmp_status st = gather_tables<T>(d, L, long_rows, s);
+        if (st != PMP_OK) return st;
     }
     if (d.binned) {
         // link blocks balanced by nonzeros, stream blocks by count; tile
@@ -801,7 +818,7 @@ AdjLayout adj_plan(int m, int n, long long ymsgs, long long smsgs, int K, int s,
 AdjLayout adj_plan_for(const pmp_handle *h, int K, int s)
 {
     const bool f32 = h->dtype == PMP_F32;
-    const int binned = f32 ? h->df.binned : h->dd.binned, staged = f32 ? h->df.staged : h->dd.staged;
+    const int binned = f32 ? h->df.binned : h->dd.binned, staged = f32 ? h->df.staged_adj : h->dd.staged_adj;
     return adj_plan(h->m, h->n, staged ? h->m : binned ? h->nnz : 0, staged ? h->n : binned ? h->nnz : 0, K, s,
                     f32 ? 4 : 8);
 }
@@ -847,6 +864,14 @@ pmp_status forward_ckpt_impl(pmp_handle *h, int K, int s, char *ws, double *J)
     const AdjLayout L = adj_plan_for(h, K, s);
     hipStream_t st = h->stream;
     pmp_status rc;
+    // A staged instance whose reverse passes gather: their blocks, on first use.
+    if (d.staged && !d.staged_adj && d.nlb == 0) {
+        rc = gather_tables<T>(d, plan(d.m, d.n, d.nnz, sizeof(T), h->prm.layout), false, st);
+        if (rc != PMP_OK) {
+            d.nlb = 0;
+            return rc;
+        }
+    }
     launch_ctl_clear_done(h->ctl, st);
     // v from (b, u), and the binned layout's link messages from v (between
     // checks that layout keeps v in its messages only)
@@ -897,7 +922,7 @@ pmp_status backward_impl(pmp_handle *h, T *gc, T *gw)
     if (h->n) HIP_TRY(hipMemcpyAsync(d.x, ws + L.xK, (size_t)h->n * sizeof(T), hipMemcpyDeviceToDevice, st));
     launch_adj_init<T>(d, a, st);
     auto ybar_messages = [&] {      // after ybar changed outside the sums' own kernels
-        if (d.staged) launch_staged_adj_cast<T>(d, a, my, st);
+        if (d.staged_adj) launch_staged_adj_cast<T>(d, a, my, st);
         else if (d.binned) launch_bin_adj_emit<T>(d, a, my, st);
     };
     ybar_messages();                // ybar = 0
@@ -924,7 +949,7 @@ pmp_status backward_impl(pmp_handle *h, T *gc, T *gw)
         for (int t = t1; t > t0; --t) {
             const T *xt = tape_x(t - t0 - 1);
             const uint8_t *mu_prev = t - 1 > t0 ? tape_mu + (size_t)(t - 2 - t0) * h->m : nullptr;
-            if (d.staged) {
+            if (d.staged_adj) {
                 launch_staged_adj_stream<T>(d, a, xt, t == K, my, ms, st);
                 launch_staged_adj_link<T>(d, a, mu_prev, ms, my, st);
             } else if (d.binned) {

@@ -183,6 +183,7 @@ struct Dev {
     // links and Q stream blocks of at most SB streams tile R into P x Q tiles.
     int binned;                     // 1: iterations use the binned kernels
     int staged;                     // 1: the passes gather from LDS (pmp_staged.h)
+    int staged_adj;                 // 1: those of reverse mode too
     StagedSide ss, sl;              // its stream and link side
     double *lsum;                   // [sl.S m] partial link sums
     int resident;                   // > 0: iterations run on chip in this many workgroups

@@ -255,7 +255,8 @@ __global__ __launch_bounds__(kBlock) void k_staged_link(Dev<T> d)
 }
 
 // Reverse mode: R^T ybar and R Sbar in the same tables.  ybar and Sbar are
-// staged in the problem's precision (yt, st), as the binned messages are.
+// staged in the problem's precision (yt, st), as the binned messages are: for
+// FP64 problems, and FP32 ones that would otherwise be binned (Dev::staged_adj).
 template <typename T>
 __global__ __launch_bounds__(kST) void k_staged_adj_stream(Dev<T> d, AdjDev a, const T *xt, int last,
                                                            const T *yt, T *st)
