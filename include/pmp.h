@@ -165,7 +165,11 @@ pmp_status pmp_setup(const pmp_problem *problem, const pmp_params *params,
 
 /* Queue k iterations on the handle's stream (asynchronous).  rho balancing
  * runs at multiples of adapt_every; no stop test.  The last iteration also
- * computes ||r|| and ||s||, read by pmp_residuals. */
+ * computes ||r|| and ||s||, read by pmp_residuals.  A small instance's
+ * iterations run in workgroups that wait for each other; a wait that exceeds
+ * its bound (2^26 polls) ends them, the iterate is lost, and every call that uses
+ * it returns PMP_ERR_HIP (pmp_iterate once it is known on the host) until
+ * pmp_set_state. */
 pmp_status pmp_iterate(pmp_handle *h, int32_t k);
 
 /* Synchronise and return the residuals of the last check and the iteration

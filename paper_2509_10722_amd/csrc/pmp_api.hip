@@ -229,6 +229,7 @@ struct pmp_handle {
     Dev<float> df{};
     Dev<double> dd{};
     int layout = PMP_LAYOUT_GATHER;   // the layout chosen at setup
+    int *group_failed = nullptr;   // pinned, behind ctl_host: a barrier of the on-chip iterations gave up
     Ctl *ctl = nullptr;            // device
     Ctl *ctl_host = nullptr;       // pinned, kSlots entries
     hipEvent_t ev[kSlots] = {};
@@ -245,6 +246,20 @@ struct pmp_handle {
 };
 
 namespace {
+
+// For calls that use the iterate, after they have waited for the stream.
+pmp_status group_status(const pmp_handle *h)
+{
+    if (*(volatile const int *)h->group_failed)
+        return fail(PMP_ERR_HIP, "on-chip iterations: a barrier wait exceeded its bound; the iterate is lost until "
+                                 "pmp_set_state");
+    return PMP_OK;
+}
+#define GROUP_TRY(h)                                \
+    do {                                            \
+        const pmp_status gs_ = group_status(h);     \
+        if (gs_ != PMP_OK) return gs_;              \
+    } while (0)
 
 template <typename T>
 Dev<T> &dev_of(pmp_handle *h);
@@ -733,10 +748,11 @@ pmp_status solve_impl(pmp_handle *h, pmp_result *out)
         const int slot = (int)(waited % kSlots);
         HIP_TRY(hipEventSynchronize(h->ev[slot]));
         ++waited;
-        if (h->ctl_host[slot].done) done = true;
+        if (h->ctl_host[slot].done || group_status(h) != PMP_OK) done = true;
     }
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(s));
+    GROUP_TRY(h);
     Ctl c;
     if (waited > 0) c = h->ctl_host[(waited - 1) % kSlots];   // the last chunk's, or the one that was done
     else HIP_TRY(hipMemcpy(&c, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
@@ -747,6 +763,7 @@ pmp_status solve_impl(pmp_handle *h, pmp_result *out)
         HIP_TRY(hipStreamSynchronize(s));
         HIP_TRY(hipMemcpy(&c, h->ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
     }
+    GROUP_TRY(h);
     pmp_status st = c.done ? (pmp_status)c.status : PMP_NOT_CONVERGED;
     if (out) {
         out->iterations = c.iter - start;
@@ -896,6 +913,7 @@ pmp_status forward_ckpt_impl(pmp_handle *h, int K, int s, char *ws, double *J)
     double jv = 0.0;
     HIP_TRY(hipMemcpyAsync(&jv, ws + L.J, 8, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
+    GROUP_TRY(h);
     if (J) *J = jv;
     h->adj_ws = ws;
     h->adj_K = K;
@@ -1068,6 +1086,7 @@ pmp_status time_kernels_impl(pmp_handle *h, int k, double *ms)
     }
     for (auto &f : ev) (void)hipEventDestroy(f);
     if (e != hipSuccess) return fail(PMP_ERR_HIP, "hipStreamSynchronize: %s", hipGetErrorString(e));
+    GROUP_TRY(h);
     for (int i = 0; i < 4; ++i) ms[i] = cnt[i] ? acc[i] / cnt[i] : 0.0;
     return PMP_OK;
 }
@@ -1142,9 +1161,12 @@ pmp_status pmp_setup(const pmp_problem *problem, const pmp_params *params, void 
         return cleanup(fail(PMP_ERR_HIP, "hipGetSymbolAddress of the pruning scratch failed"));
     if (hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) != hipSuccess)
         return cleanup(fail(PMP_ERR_HIP, "hipStreamCreateWithFlags failed"));
-    if (hipHostMalloc((void **)&h->ctl_host, sizeof(Ctl) * kSlots, hipHostMallocDefault) !=
+    if (hipHostMalloc((void **)&h->ctl_host, sizeof(Ctl) * kSlots + sizeof(int), hipHostMallocDefault) !=
         hipSuccess)
         return cleanup(fail(PMP_ERR_HIP, "hipHostMalloc failed"));
+    h->group_failed = (int *)(h->ctl_host + kSlots);
+    *h->group_failed = 0;
+    h->df.res_failed = h->dd.res_failed = h->group_failed;
     for (auto &e : h->ev)
         if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
             return cleanup(fail(PMP_ERR_HIP, "hipEventCreate failed"));
@@ -1160,6 +1182,7 @@ pmp_status pmp_iterate(pmp_handle *h, int32_t k)
     if (!h) return fail(PMP_ERR_INVALID, "handle is NULL");
     if (k < 0) return fail(PMP_ERR_INVALID, "k must be >= 0");
     if (k == 0) return PMP_OK;
+    GROUP_TRY(h);   // (known from an earlier call; the kernels refuse to go on by themselves)
     launch_ctl_clear_done(h->ctl, h->stream);
     if (h->dtype == PMP_F32) enqueue_iterations<float>(h, k, h->stream);
     else enqueue_iterations<double>(h, k, h->stream);
@@ -1176,6 +1199,7 @@ pmp_status pmp_residuals(pmp_handle *h, double *r_norm, double *s_norm, int64_t 
     if (r_norm) *r_norm = c.r_norm;
     if (s_norm) *s_norm = c.s_norm;
     if (iteration) *iteration = c.iter;
+    GROUP_TRY(h);
     if (c.status == PMP_ERR_NUMERIC)
         return fail(PMP_ERR_NUMERIC, "non-finite residual at iteration %lld", c.iter);
     return PMP_OK;
@@ -1196,7 +1220,7 @@ pmp_status pmp_get_solution(pmp_handle *h, void *x, void *lambda, void *slack)
         launch_solution<double>(h->dd, (double *)x, (double *)lambda, (double *)slack, h->stream);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(h->stream));
-    return PMP_OK;
+    return group_status(h);
 }
 
 pmp_status pmp_get_path_prices(pmp_handle *h, void *pi)
@@ -1208,7 +1232,7 @@ pmp_status pmp_get_path_prices(pmp_handle *h, void *pi)
         launch_path_prices<double>(h->dd, (double *)pi, h->stream);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(h->stream));
-    return PMP_OK;
+    return group_status(h);
 }
 
 pmp_status pmp_prune_workspace_size(pmp_handle *h, size_t *bytes)
@@ -1241,6 +1265,7 @@ pmp_status pmp_prune(pmp_handle *h, const uint8_t *failed, void *workspace,
                                  (double *)w, utility, link_map, stream_map, (char *)state, sz,
                                  h->stream);
     if (e != hipSuccess) return fail(PMP_ERR_HIP, "pruning failed: %s", hipGetErrorString(e));
+    GROUP_TRY(h);
     for (int i = 0; i < 3; ++i) sizes[i] = sz[i];
     return PMP_OK;
 }
@@ -1287,7 +1312,7 @@ pmp_status pmp_get_state(pmp_handle *h, void *state)
     HIP_TRY(hipMemcpyAsync(p + n + 3 * m, &h->ctl->rho, 8, hipMemcpyDeviceToDevice, s));
     HIP_TRY(hipMemcpyAsync(p + n + 3 * m + 8, &h->ctl->iter, 8, hipMemcpyDeviceToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));
-    return PMP_OK;
+    return group_status(h);
 }
 
 pmp_status pmp_set_state(pmp_handle *h, const void *state)
@@ -1315,6 +1340,11 @@ pmp_status pmp_set_state(pmp_handle *h, const void *state)
     std::memcpy(&it, tail + 8, 8);
     if (!(rho > 0.0) || !std::isfinite(rho)) return fail(PMP_ERR_INVALID, "state rho must be > 0");
     if (it < 0) return fail(PMP_ERR_INVALID, "state iteration must be >= 0");
+    if (*h->group_failed) {   // an expired wait: every workgroup's words start over
+        ResSync *rs = h->dtype == PMP_F32 ? h->df.rsync : h->dd.rsync;
+        launch_fill_int((int *)rs, 0, sizeof(ResSync) / 4, s);
+        *h->group_failed = 0;
+    }
     // Re-seed the control block (keeping the tolerances) and v = b - u.
     const double J = (double)h->nnz + (double)h->m;
     launch_ctl_init(h->ctl, rho, h->prm.eps_abs * std::sqrt(J), h->prm.eps_rel, h->prm.mu, h->prm.gamma,
@@ -1382,7 +1412,7 @@ pmp_status pmp_history(pmp_handle *h, double *out, int32_t capacity, int32_t *co
         out[4 * i + 3] = buf[(size_t)idx].rho;
     }
     *count = take;
-    return PMP_OK;
+    return group_status(h);
 }
 
 pmp_status pmp_update_capacity(pmp_handle *h, const void *c_new)

@@ -122,7 +122,7 @@ struct ResSync {
     unsigned win, pad0[63];         // XCD + 1 whose workgroups form the group
     unsigned flag[64];              // last barrier each workgroup has reached
     unsigned base, pad1[63];        // barriers passed by the launches before
-    unsigned solo, exits, abort, pad2[61];
+    unsigned abort, exits, solo, pad2[61];
     double part[32][8];             // residual partials of a check, per workgroup
 };
 
@@ -188,6 +188,7 @@ struct Dev {
     double *lsum;                   // [sl.S m] partial link sums
     int resident;                   // > 0: iterations run on chip in this many workgroups
     ResSync *rsync;                 // their meeting point (pmp_resident.h)
+    int *res_failed;                // pinned host word: a barrier among them gave up
     int P, Q, LB, SB;
     int SR;                         // stream blocks per dispatch round of the stream pass
     int CUs;                        // compute units of the device (binned layout)

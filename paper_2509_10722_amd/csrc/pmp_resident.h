@@ -53,7 +53,8 @@ constexpr int kResSteps1 = 4, kResSteps4 = 12;       // steps past the slots (re
 constexpr size_t kResLds = 159 * 1024;               // LDS for the staged vectors
 constexpr unsigned long long kRollTicks = 400000;    // 4 ms of the 100 MHz wall clock
 constexpr unsigned kResPolls = 1u << 26;             // bound of a phase barrier's wait
-constexpr unsigned kOpen = 0, kSolo = 99;            // ResSync::win: nobody yet / no group
+// ResSync::win: nobody yet / no group / a barrier gave up, no more launches
+constexpr unsigned kOpen = 0, kSolo = 99, kGone = 98;
 
 template <typename V>
 __device__ __forceinline__ V ld_agent(const V *p)
@@ -172,8 +173,13 @@ __device__ __forceinline__ void stage(const T *src, T *dst, int cnt)
 
 // Barrier of the group's workgroups (`epoch` counts them); false if it gave
 // up.  Every workgroup stores its epoch in its own word, and one wave of each
-// reads all the words until they have it: no chain of atomic adds.
-__device__ __forceinline__ bool group_sync(ResSync *rs, int role, int G, unsigned epoch, int *s_ok)
+// reads all the words until they have it: no chain of atomic adds.  A wait of
+// more than kResPolls polls ends the launch: `abort` makes the others leave too,
+// and closes the roll calls of the launches after it, since the workgroups may
+// stand at different phases of an iteration and their words at different
+// barriers; the host's word has the calls that read the iterate say so
+// (pmp_set_state clears both).
+__device__ __forceinline__ bool group_sync(ResSync *rs, int *failed, int role, int G, unsigned epoch, int *s_ok)
 {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's stores are in the L2
     __syncthreads();
@@ -185,7 +191,10 @@ __device__ __forceinline__ bool group_sync(ResSync *rs, int role, int G, unsigne
         unsigned polls = 0;
         while (!__all(lane >= G || (int)(ld_agent(&rs->flag[lane]) - epoch) >= 0))
             if (++polls > kResPolls || ld_agent(&rs->abort)) {
-                if (lane == 0) atomicExch(&rs->abort, 1u);
+                if (lane == 0) {
+                    atomicExch(&rs->abort, 1u);
+                    __hip_atomic_store(failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                }
                 ok = false;
                 break;
             }
@@ -387,7 +396,7 @@ __global__ __launch_bounds__(kRT) void k_resident(Dev<T> d, ResSync *rs, int G, 
             if (ONE) {
                 __syncthreads();
             } else {
-                if (!(ok = group_sync(rs, role, G, ++epoch, &s_ok))) break;
+                if (!(ok = group_sync(rs, d.res_failed, role, G, ++epoch, &s_ok))) break;
                 stage<T>(d.x, xs, n);
             }
             if (has_l) {
@@ -426,7 +435,7 @@ __global__ __launch_bounds__(kRT) void k_resident(Dev<T> d, ResSync *rs, int G, 
             if (ONE) {
                 __syncthreads();
             } else {
-                if (!(ok = group_sync(rs, role, G, ++epoch, &s_ok))) break;
+                if (!(ok = group_sync(rs, d.res_failed, role, G, ++epoch, &s_ok))) break;
                 stage<T>(d.v, vs, m);
             }
             if (check) {
@@ -454,7 +463,7 @@ __global__ __launch_bounds__(kRT) void k_resident(Dev<T> d, ResSync *rs, int G, 
                     if (ONE) {
                         __syncthreads();
                     } else {
-                        if (!(ok = group_sync(rs, role, G, ++epoch, &s_ok))) break;
+                        if (!(ok = group_sync(rs, d.res_failed, role, G, ++epoch, &s_ok))) break;
                         stage<T>(d.v, vs, m);
                     }
                 }
@@ -473,22 +482,17 @@ __global__ __launch_bounds__(kRT) void k_resident(Dev<T> d, ResSync *rs, int G, 
             d.y_prev[l] = yp;
             d.ps_prev[l] = pp;
         }
-        if (tid == 0) {
-            if (!ok) {                  // a barrier gave up: report it like the batch does
-                c.done = 1;
-                c.status = PMP_ERR_HIP;
-            }
-            if (role == 0 || !ok) *d.ctl = c;
-            if (!ONE && role == 0) rs->base = epoch;
+        if (tid == 0 && role == 0 && ok) {
+            *d.ctl = c;
+            if (!ONE) rs->base = epoch;
         }
     }
     // the last workgroup to leave clears the counters for the next launch
     if (!ONE && tid == 0) {
         if (atomicAdd(&rs->exits, 1u) == gridDim.x - 1u) {
             for (int k = 0; k < 8; ++k) atomicExch(&rs->cnt[k * 64], 0u);
-            atomicExch(&rs->win, kOpen);
+            atomicExch(&rs->win, ld_agent(&rs->abort) ? kGone : kOpen);
             atomicExch(&rs->solo, 0u);
-            atomicExch(&rs->abort, 0u);
             atomicExch(&rs->exits, 0u);
         }
     }
