@@ -647,7 +647,9 @@ void enqueue_iterations(pmp_handle *h, int k, hipStream_t s)
     Dev<T> &d = dev_of<T>(h);
     const int adapt = h->prm.adapt_every;
     if (d.resident) {
-        launch_resident<T>(d, k, 0, adapt, s);
+        const int most = d.resident > 1 ? kResIters : k;
+        for (int left = k; left > 0; left -= most)
+            launch_resident<T>(d, std::min(left, most), left <= most, 0, adapt, s);
         h->iter_enq = h->iter_fin = h->iter_enq + k;
         return;
     }
@@ -720,7 +722,7 @@ pmp_status solve_impl(pmp_handle *h, pmp_result *out)
     // A chunk is a replay of the captured check_every iterations, or, for a
     // small instance, about a thousand iterations in one launch (which leaves
     // at the stop rule by itself).
-    const long long per = d.resident ? ce * std::max<long long>(1, 1000 / ce) : ce;
+    const long long per = d.resident ? ce * std::max<long long>(1, kResIters / ce) : ce;
     const long long leftover = budget % ce;
     const long long whole = budget - leftover;
     const long long chunks = (whole + per - 1) / per;
@@ -729,7 +731,7 @@ pmp_status solve_impl(pmp_handle *h, pmp_result *out)
     while (!done && waited < chunks) {
         while (launched < chunks && launched - waited < kSlots) {
             if (d.resident)
-                launch_resident<T>(d, std::min(per, whole - launched * per), ce, h->prm.adapt_every, s);
+                launch_resident<T>(d, (int)std::min(per, whole - launched * per), true, ce, h->prm.adapt_every, s);
             else {
                 const long long end = start + align + (launched + 1) * ce;
                 const bool balance = h->prm.adapt_every > 0 && end % h->prm.adapt_every == 0;

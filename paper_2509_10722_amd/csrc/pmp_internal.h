@@ -119,10 +119,10 @@ enum LinkMode : int { kPlain = 0, kSave = 1, kCheck = 2 };
 // each polled or added to on a line of its own.
 struct ResSync {
     unsigned cnt[8 * 64];           // workgroups started on each XCD
-    unsigned win, pad0[63];         // XCD + 1 whose workgroups form the group
+    unsigned win, pad0[63];         // which workgroups form the group
     unsigned flag[64];              // last barrier each workgroup has reached
     unsigned base, pad1[63];        // barriers passed by the launches before
-    unsigned abort, exits, solo, pad2[61];
+    unsigned abort, exits, pad2[62];
     double part[32][8];             // residual partials of a check, per workgroup
 };
 
@@ -340,9 +340,13 @@ void launch_bin_adj_emit(const Dev<T> &d, const AdjDev &a, T *my, hipStream_t s)
 int resident_plan(int m, int n, int longest_link, int longest_route, size_t sz);
 template <typename T>
 hipError_t resident_configure(const Dev<T> &d);
-// `iters` iterations; ce > 0: a check with the stop rule at multiples of ce.
+// `iters` iterations, with end_check a check at the last (a single workgroup
+// always ends in one); ce > 0: a check with the stop rule at multiples of ce.
+// Callers keep a launch of several workgroups to about kResIters iterations: one
+// that finds the GPU busy may run on fewer than it has rows for.
+constexpr int kResIters = 1000;
 template <typename T>
-void launch_resident(const Dev<T> &d, long long iters, int ce, int adapt, hipStream_t s);
+void launch_resident(const Dev<T> &d, int iters, bool end_check, int ce, int adapt, hipStream_t s);
 
 // Passes that gather from LDS (pmp_staged.h).  staged_plan: the shapes for
 // these sizes; false where the other layouts are the better ones.

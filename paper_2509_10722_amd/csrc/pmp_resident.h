@@ -22,13 +22,18 @@
 // tickets once all have started), the first XCD to deal G wins, and the rest
 // leave.  All members are then running, so the phase barriers complete.  If
 // no XCD gets that far in kRollTicks (the GPU is shared with other long
-// kernels), one workgroup runs the iterations by itself from memory.
+// kernels), the workgroups that have started on the XCD with the most of them
+// run this launch's iterations, rows dealt out in turn and everything read
+// from memory; a launch has about a thousand iterations at most (launch_resident's
+// callers), so the next one soon calls the roll again.  30,000 x 30,000: 41 us an
+// iteration on 24 of the 30 workgroups, 62 on 8, 113 on 4, 392 on one alone.
 //
 // What bounds it is latency: LDS round trips, the barriers, the FP64 divide
 // and root of the prox.  Measured on MI355X, us an iteration against the two
 // gather passes: 200 links x 1,000 streams 2.0 (9.1) in FP64, 2.1 (9.5) in
-// FP32; 8,000 x 8,000 with 64,000 nonzeros 5.7 (9.8); 30,000 x 30,000 with
-// 300,000 nonzeros 7.8 (11.3), the largest FP32 size whose vector fits the LDS.
+// FP32; 8,000 x 8,000 with 64,000 nonzeros 5.2 (9.8); 30,000 x 30,000 with
+// 300,000 nonzeros 7.5 (11.3).  The largest side has 32,768 rows (a lane each in 32
+// workgroups); the LDS holds 40,696 in FP32, 20,344 in FP64.
 //
 // Every sum keeps the gather layout's order (run_sum) and every update its
 // arithmetic (stream_core, link_core), so the iterates are the same bit for
@@ -53,8 +58,9 @@ constexpr int kResSteps1 = 4, kResSteps4 = 12;       // steps past the slots (re
 constexpr size_t kResLds = 159 * 1024;               // LDS for the staged vectors
 constexpr unsigned long long kRollTicks = 400000;    // 4 ms of the 100 MHz wall clock
 constexpr unsigned kResPolls = 1u << 26;             // bound of a phase barrier's wait
-// ResSync::win: nobody yet / no group / a barrier gave up, no more launches
-constexpr unsigned kOpen = 0, kSolo = 99, kGone = 98;
+// ResSync::win: nobody yet; XCD + 1 of a whole group; being closed; a barrier
+// gave up, no more launches; kFew + 8 (g - 1) + XCD: its first g workgroups
+constexpr unsigned kOpen = 0, kClosing = 97, kGone = 98, kFew = 99;
 
 template <typename V>
 __device__ __forceinline__ V ld_agent(const V *p)
@@ -222,113 +228,162 @@ __device__ __forceinline__ void reduce_parts(double r2, double ss, bool rel, con
         }
 }
 
-// run_sum of tab[idx[b..e)) from memory.
+// run_sum of tab[idx[b..e)) from memory (tab: written by the group).
 template <typename T>
 __device__ __forceinline__ double run_sum_idx(const T *tab, const int *idx, int b, int e)
 {
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     int k = b;
     for (; k + 3 < e; k += 4) {
-        s0 += (double)tab[idx[k]];
-        s1 += (double)tab[idx[k + 1]];
-        s2 += (double)tab[idx[k + 2]];
-        s3 += (double)tab[idx[k + 3]];
+        const T t0 = ld_agent(tab + idx[k]), t1 = ld_agent(tab + idx[k + 1]);
+        const T t2 = ld_agent(tab + idx[k + 2]), t3 = ld_agent(tab + idx[k + 3]);
+        s0 += (double)t0;
+        s1 += (double)t1;
+        s2 += (double)t2;
+        s3 += (double)t3;
     }
-    for (; k < e; ++k) s0 += (double)tab[idx[k]];
+    for (; k < e; ++k) s0 += (double)ld_agent(tab + idx[k]);
     return (s0 + s1) + (s2 + s3);
 }
 
-// The iterations by one workgroup straight from memory (no group was formed).
-template <typename T>
-__device__ void run_alone(const Dev<T> &d, Ctl &c, double *sred, double *parts, long long iters, int ce,
-                          int adapt)
+// The group's partials of a check, added in the same order by each workgroup
+// (thread 0).
+__device__ __forceinline__ void add_parts(ResSync *rs, int G, double *parts)
 {
-    const int tid = threadIdx.x;
+    for (int k = 0; k < 5; ++k) {
+        double t = 0.0;
+        for (int g = 0; g < G; ++g) t += ld_agent(&rs->part[g][k]);
+        parts[k] = t;
+    }
+}
+
+// The iterations by a smaller group than they were laid out for, from memory.
+template <typename T>
+__device__ bool run_few(const Dev<T> &d, ResSync *rs, int role, int G, unsigned &epoch, Ctl &c, HistEntry &h,
+                        double *sred, double *parts, int *s_ok, int iters, int end, int ce, int adapt)
+{
+    const int first = role * kRT + (int)threadIdx.x, step = G * kRT;
     const long long it0 = c.iter;
-    for (long long i = 1; i <= iters; ++i) {
+    for (int i = 1; i <= iters; ++i) {
         const long long it = it0 + i;
         const bool stop = ce > 0 && it % ce == 0;
-        const bool check = i == iters || stop || (adapt > 0 && it % adapt == 0);
+        const bool check = i == end || stop || (adapt > 0 && it % adapt == 0);
+        const bool rel = check && c.eps_rel > 0.0;
         const double irho = c.irho;
         double ss = 0.0, r2 = 0.0, q[3] = {0.0, 0.0, 0.0};
-        for (int j = tid; j < d.n; j += kRT) {
+        for (int j = first; j < d.n; j += step) {
             const int b = d.col_ptr[j], L = d.col_ptr[j + 1] - b;
             const double acc = run_sum_idx<T>(d.v, d.row_idx, b, b + L);
             ss += stream_update<T, true>(d, j, L, acc, irho);
-            const double xj = (double)d.x[j], aj = (double)d.a[j];
-            q[0] += (double)L * xj * xj;
-            q[1] += (double)L * aj * aj;
+            if (rel) {
+                const double xj = (double)d.x[j], aj = (double)d.a[j];
+                q[0] += (double)L * xj * xj;
+                q[1] += (double)L * aj * aj;
+            }
         }
-        __syncthreads();
-        for (int l = tid; l < d.m; l += kRT) {
+        if (!group_sync(rs, d.res_failed, role, G, ++epoch, s_ok)) return false;
+        for (int l = first; l < d.m; l += step) {
             const int b = d.row_ptr[l], deg = d.row_ptr[l + 1] - b;
             const double acc = run_sum_idx<T>(d.x, d.col_idx, b, b + deg);
             link_update<T, kCheck>(d, l, deg, acc, r2, ss);
-            const double dg = (double)deg, bl = (double)d.b[l], z = (double)d.zs[l], ul = (double)d.u[l];
-            q[0] += d.ps_prev[l] * d.ps_prev[l];
-            q[1] += z * z - dg * bl * bl - 2.0 * bl * z;
-            q[2] += (dg + 1.0) * ul * ul;
+            if (rel) {
+                const double dg = (double)deg, bl = (double)d.b[l], z = (double)d.zs[l], ul = (double)d.u[l];
+                q[0] += d.ps_prev[l] * d.ps_prev[l];
+                q[1] += z * z - dg * bl * bl - 2.0 * bl * z;
+                q[2] += (dg + 1.0) * ul * ul;
+            }
+        }
+        if (check) reduce_parts(r2, ss, rel, q, sred, rs->part[role]);
+        if (!group_sync(rs, d.res_failed, role, G, ++epoch, s_ok)) return false;
+        if (!check) continue;
+        if (threadIdx.x == 0) {
+            add_parts(rs, G, parts);
+            finalize(&c, h, it - c.iter, stop ? 1 : 0, parts[0], parts[1], rel ? parts + 2 : nullptr);
+            if (role == 0) d.hist[(c.nhist - 1) % kHist] = h;
         }
         __syncthreads();
-        if (!check) continue;
-        reduce_parts(r2, ss, true, q, sred, parts);
-        if (tid == 0)
-            finalize(&c, d.hist[c.nhist % kHist], it - c.iter, stop ? 1 : 0, parts[0], parts[1],
-                     c.eps_rel > 0.0 ? parts + 2 : nullptr);
-        __syncthreads();
-        if (c.ratio != 1.0)
-            for (int l = tid; l < d.m; l += kRT) {
+        if (c.ratio != 1.0) {
+            for (int l = first; l < d.m; l += step) {
                 T ut = d.u[l];
                 d.v[l] = link_rescale<T>(d.b[l], ut, c.ratio);
                 d.u[l] = ut;
             }
-        __syncthreads();
-        if (c.done) return;
+            if (!group_sync(rs, d.res_failed, role, G, ++epoch, s_ok)) return false;
+        }
+        if (c.done) break;
     }
+    return true;
 }
 
 // `iters` iterations from the state in memory.  Residuals (and rho balancing
 // where due) at iteration counts that are multiples of adapt_every and at the
-// last iteration; with ce > 0 at multiples of ce too, where the stop rule ends
-// the run.  ONE: a single workgroup; else a group of G on one XCD.
+// iteration `end` (0: at none); with ce > 0 at multiples of ce too, where the
+// stop rule ends the run.  ONE: a single workgroup, which ends in a check; else a
+// group of G on one XCD.
 template <typename T, bool ONE>
-__global__ __launch_bounds__(kRT) void k_resident(Dev<T> d, ResSync *rs, int G, long long iters, int ce,
-                                                  int adapt)
+__global__ __launch_bounds__(kRT) void k_resident(Dev<T> d, ResSync *rs, int G, int iters, int end,
+                                                  int ce, int adapt)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ Ctl c;
     __shared__ HistEntry h;
     __shared__ double sred[kRWaves], parts[5];
-    __shared__ int s_role, s_ok;
+    __shared__ int s_role, s_size, s_ok;
+    __shared__ long long s_last;            // iteration count at the end
     const int tid = threadIdx.x, m = d.m, n = d.n;
     if (ONE) {
         if (d.ctl->done) return;
     } else {
         if (tid == 0) {
-            int role = -1;
+            int role = -1, size = 0;
             if (!ld_agent(&d.ctl->done)) {
                 const unsigned x = (unsigned)xcc_id() % 8u;
                 const unsigned t = atomicAdd(&rs->cnt[x * 64], 1u);
                 if (t == (unsigned)G - 1u) atomicCAS(&rs->win, kOpen, x + 1u);
                 const unsigned long long t0 = wall_clock64();
                 unsigned w;
-                while ((w = ld_agent(&rs->win)) == kOpen)
-                    if (wall_clock64() - t0 > kRollTicks) atomicCAS(&rs->win, kOpen, kSolo);
-                if (w == x + 1u && t < (unsigned)G) role = (int)t;
-                else if (w == kSolo && atomicAdd(&rs->solo, 1u) == 0u) role = (int)kSolo;
+                while ((w = ld_agent(&rs->win)) == kOpen || w == kClosing)
+                    if (w == kOpen && wall_clock64() - t0 > kRollTicks &&
+                        atomicCAS(&rs->win, kOpen, kClosing) == kOpen) {
+                        // (every ticket's workgroup runs and waits in this loop)
+                        unsigned most = 0, on = 0;
+                        for (unsigned k = 0; k < 8; ++k) {
+                            const unsigned g = min(ld_agent(&rs->cnt[k * 64]), (unsigned)G);
+                            if (g > most) {
+                                most = g;
+                                on = k;
+                            }
+                        }
+                        atomicExch(&rs->win, kFew + 8u * (most - 1u) + on);
+                    }
+                if (w == x + 1u) size = G;
+                else if (w >= kFew && (w - kFew) % 8u == x) size = (int)((w - kFew) / 8u + 1u);
+                if (t < (unsigned)size) role = (int)t;
             }
+            s_size = size;
             s_role = role;
         }
         __syncthreads();
     }
     const int role = ONE ? 0 : s_role;
     if (role >= 0) {
-        if (tid == 0) c = *d.ctl;
+        if (tid == 0) {
+            c = *d.ctl;
+            s_last = c.iter + iters;
+        }
         __syncthreads();
     }
-    if (!ONE && role == (int)kSolo) {
-        run_alone<T>(d, c, sred, parts, iters, ce, adapt);
-        if (tid == 0) *d.ctl = c;
+    // barriers are numbered on from the last launch: the words need no reset
+    unsigned epoch = ONE || role < 0 ? 0u : rs->base;
+    bool ok = true;
+    if (!ONE && role >= 0 && s_size < G) {
+        // The instance is the kernel's first argument, read here through a pointer
+        // the compiler knows nothing of: it loads what run_few uses in this branch,
+        // and the iterations below keep those registers (82 -> 39 of them spilled;
+        // 8,000 x 8,000 5.34 -> 5.16 us an iteration).
+        const Dev<T> *dp = (const Dev<T> *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(dp));
+        ok = run_few<T>(*dp, rs, role, s_size, epoch, c, h, sred, parts, &s_ok, iters, end, ce, adapt);
     } else if (role >= 0) {
         T *xs = (T *)lds;
         T *vs = ONE ? xs + ((n + 8) & ~7) : xs;   // a group needs one of them at a time
@@ -360,9 +415,6 @@ __global__ __launch_bounds__(kRT) void k_resident(Dev<T> d, ResSync *rs, int G, 
             yp = d.y_prev[l];
             pp = d.ps_prev[l];
         }
-        // barriers are numbered on from the last launch: the words need no reset
-        unsigned epoch = ONE ? 0u : rs->base;
-        bool ok = true;
         stage<T>(d.v, vs, m);
         if (ONE && tid == 0) xs[n] = T(0);
         const long long it0 = c.iter;
@@ -371,11 +423,11 @@ __global__ __launch_bounds__(kRT) void k_resident(Dev<T> d, ResSync *rs, int G, 
         // an iteration)
         int to_stop = ce > 0 ? ce - (int)(it0 % ce) : 0;
         int to_adapt = adapt > 0 ? adapt - (int)(it0 % adapt) : 0;
-        for (long long i = 1; i <= iters; ++i) {
+        for (int i = 1; i <= iters; ++i) {
             const bool stop = --to_stop == 0, balance = --to_adapt == 0;
             if (stop) to_stop = ce;
             if (balance) to_adapt = adapt;
-            const bool check = i == iters || stop || balance;
+            const bool check = (ONE ? i == iters : i == end) || stop || balance;
             const double irho = c.irho;
             double ss = 0.0, r2 = 0.0;
             if (has_s) {
@@ -439,15 +491,10 @@ __global__ __launch_bounds__(kRT) void k_resident(Dev<T> d, ResSync *rs, int G, 
                 stage<T>(d.v, vs, m);
             }
             if (check) {
-                // every workgroup adds the group's partials in the same order
-                // and takes the same decisions on its own copy of the control block
+                // every workgroup takes the same decisions on its own copy of
+                // the control block
                 if (tid == 0) {
-                    if (!ONE)
-                        for (int k = 0; k < 5; ++k) {
-                            double t = 0.0;
-                            for (int g = 0; g < G; ++g) t += ld_agent(&rs->part[g][k]);
-                            parts[k] = t;
-                        }
+                    if (!ONE) add_parts(rs, G, parts);
                     finalize(&c, h, it0 + i - c.iter, stop ? 1 : 0, parts[0], parts[1],
                              c.eps_rel > 0.0 ? parts + 2 : nullptr);
                     if (role == 0) d.hist[(c.nhist - 1) % kHist] = h;
@@ -482,17 +529,17 @@ __global__ __launch_bounds__(kRT) void k_resident(Dev<T> d, ResSync *rs, int G, 
             d.y_prev[l] = yp;
             d.ps_prev[l] = pp;
         }
-        if (tid == 0 && role == 0 && ok) {
-            *d.ctl = c;
-            if (!ONE) rs->base = epoch;
-        }
+    }
+    if (tid == 0 && role == 0 && ok) {
+        if (!c.done) c.iter = s_last;
+        *d.ctl = c;
+        if (!ONE) rs->base = epoch;
     }
     // the last workgroup to leave clears the counters for the next launch
     if (!ONE && tid == 0) {
         if (atomicAdd(&rs->exits, 1u) == gridDim.x - 1u) {
             for (int k = 0; k < 8; ++k) atomicExch(&rs->cnt[k * 64], 0u);
             atomicExch(&rs->win, ld_agent(&rs->abort) ? kGone : kOpen);
-            atomicExch(&rs->solo, 0u);
             atomicExch(&rs->exits, 0u);
         }
     }
@@ -533,20 +580,21 @@ hipError_t resident_configure(const Dev<T> &d)
 }
 
 template <typename T>
-void launch_resident(const Dev<T> &d, long long iters, int ce, int adapt, hipStream_t s)
+void launch_resident(const Dev<T> &d, int iters, bool end_check, int ce, int adapt, hipStream_t s)
 {
+    const int end = end_check ? iters : 0;
     const int G = d.resident;
     const size_t lds = resident_lds(d.m, d.n, G, sizeof(T));
     if (G == 1)
-        hipLaunchKernelGGL((k_resident<T, true>), dim3(1), dim3(kRT), lds, s, d, d.rsync, 1, iters, ce, adapt);
+        hipLaunchKernelGGL((k_resident<T, true>), dim3(1), dim3(kRT), lds, s, d, d.rsync, 1, iters, end, ce, adapt);
     else
-        hipLaunchKernelGGL((k_resident<T, false>), dim3(8 * G), dim3(kRT), lds, s, d, d.rsync, G, iters, ce,
-                           adapt);
+        hipLaunchKernelGGL((k_resident<T, false>), dim3(8 * G), dim3(kRT), lds, s, d, d.rsync, G, iters, end,
+                           ce, adapt);
 }
 
 template hipError_t resident_configure<float>(const Dev<float> &);
 template hipError_t resident_configure<double>(const Dev<double> &);
-template void launch_resident<float>(const Dev<float> &, long long, int, int, hipStream_t);
-template void launch_resident<double>(const Dev<double> &, long long, int, int, hipStream_t);
+template void launch_resident<float>(const Dev<float> &, int, bool, int, int, hipStream_t);
+template void launch_resident<double>(const Dev<double> &, int, bool, int, int, hipStream_t);
 
 }  // namespace pmp

@@ -75,3 +75,52 @@ def test_expired_barrier_wait_is_reported_until_set_state(dtype, queued):
     assert s.solve() == ref.solve()
     s.close()
     ref.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("few", [1, 2, 4])
+def test_fewer_workgroups_than_laid_out(few, dtype):
+    """A launch whose workgroups do not meet goes on with those that have
+    started (the word that records the group is set from the host: the first
+    `few` on XCD 0): the same iterates, balancing and residuals, for that launch
+    only."""
+    inst = _instance(5000, 4500, 2, 8)
+    s, ref = Solver(inst, dtype=dtype, eps_rel=1e-3), Solver(inst, dtype=dtype, eps_rel=1e-3)
+    for t in (s, ref):
+        t.iterate(30)
+    w, win = _meeting_words(s, 30)
+    w[win] = 99 + 8 * (few - 1)
+    for k in (137, 20):                     # with balancing steps; then a whole group again
+        for t in (s, ref):
+            t.iterate(k)
+        assert int(w[win]) == 0
+        for name, v in s.views().items():
+            assert torch.equal(v, ref.views()[name]), name
+        a, b = s.history(), ref.history()
+        assert a.shape == b.shape and np.array_equal(a[:, [0, 3]], b[:, [0, 3]])
+        assert np.allclose(a, b, rtol=1e-9, atol=0)
+    s.reset()
+    w[win] = 99 + 8 * (few - 1)
+    res, want = s.solve(), Solver(inst, dtype=dtype, eps_rel=1e-3).solve()
+    assert res["iterations"] == want["iterations"] and res["converged"] == want["converged"]
+    s.close()
+    ref.close()
+
+
+def test_long_queue_in_several_launches():
+    """More iterations than a launch takes: no check where launches meet."""
+    inst = _instance(2500, 2200, 2, 8)
+    a, b = Solver(inst), Solver(inst)
+    a.iterate(2525)
+    for k in (1000, 1000, 525):
+        b.iterate(k)
+    for name, v in a.views().items():
+        assert torch.equal(v, b.views()[name]), name
+    assert a.residuals() == b.residuals() and a.residuals()[2] == 2525
+    its = a.history()[:, 0]
+    assert np.array_equal(its, np.append(np.arange(50, 2501, 50), 2525))
+    c = Solver(inst, adapt_every=0)
+    c.iterate(2525)
+    assert np.array_equal(c.history()[:, 0], [2525])
+    for t in (a, b, c):
+        t.close()
