@@ -249,7 +249,7 @@ def bench_adjoint(args, log):
     inst = instances.adjoint(scale=args.scale).rounded(np.float32)
     K, s = 500, 25
     solver = Solver(inst, dtype=torch.float32, adapt_every=0)
-    layout = solver.layout_in_use()
+    layout, passes = solver.layout_in_use(), solver.passes_in_use()
     solver.iterate(K)
     solver.reset()
     torch.cuda.synchronize()
@@ -277,8 +277,8 @@ def bench_adjoint(args, log):
         "value": round(t_fwd + t_bwd, 4), "unit": "s", "n_gpus": 1,
         "higher_is_better": False, "dtype": "f32", "data": "synthetic",
         "config": {"workload": f"adjoint (m={inst.m}, n={inst.n}, nnz={inst.nnz})", "K": K,
-                   "checkpoint_every": s, "layout": layout, "rho": "fixed 1"},
-        "verified": "the same configuration (FP32, binned, K=500, s=25, fixed rho) against "
+                   "checkpoint_every": s, "layout": layout, "passes": passes, "rho": "fixed 1"},
+        "verified": "the same configuration (FP32, K=500, s=25, fixed rho) against "
                     "central differences (h=1e-3) of the FP64 oracle at scale 0.1 and 1: "
                     "tests/test_gpu_adjoint.py",
         "forward_s": round(t_fwd, 4), "backward_s": round(t_bwd, 4),
@@ -424,7 +424,7 @@ def bench_congested(args, log):
         deg = np.diff(inst.row_ptr)
         out[name] = {"nnz": inst.nnz, "max_link_degree": int(deg.max()),
                      "iterations": r["iterations"], "converged": r["converged"],
-                     "time_s": round(dt, 4), "layout": s.layout_in_use()}
+                     "time_s": round(dt, 4), "layout": s.layout_in_use(), "passes": s.passes_in_use()}
         s.close()
         log(f"[bench] {name}: {out[name]}")
     line = {"metric": "extra iterations to 1e-4 under congestion (Section V-C)",
@@ -577,7 +577,7 @@ def main():
     layout = {"auto": 0, "gather": 1, "binned": 2}[args.layout]
     solver = Solver(inst32, dtype=torch.float32, eps_abs=0.0, max_iter=max(1, args.warmup),
                     layout=layout)
-    used = solver.layout_in_use()
+    used, passes = solver.layout_in_use(), solver.passes_in_use()
     torch.cuda.synchronize()
     setup_s = time.perf_counter() - t0
     log(f"[bench] setup {setup_s:.2f} s")
@@ -611,13 +611,18 @@ def main():
     log(f"[bench] median of {len(runs)} runs of {args.steps} iterations: {dt:.4f} s, "
         f"{ips:.1f} it/s")
 
-    kt = solver.time_kernels(args.kernel_iters)
-    log(f"[bench] per-kernel ms (HIP events): {kt}")
     bm = bytes_model(inst.n, inst.m, inst.nnz)
-    dom = "link" if kt["link"] >= kt["stream"] else "stream"
-    achieved = bm[dom] / (kt[dom] * 1e-3) / 1e9
-    kname = {"link": "link_pass", "stream": "stream_pass"}[dom]
-    traffic = load_traffic(kname, used, args.config)
+    kt = roofline = None
+    if passes != "on-chip":     # such an instance's iterations launch no passes
+        kt = solver.time_kernels(args.kernel_iters)
+        log(f"[bench] per-kernel ms (HIP events): {kt}")
+        dom = "link" if kt["link"] >= kt["stream"] else "stream"
+        achieved = bm[dom] / (kt[dom] * 1e-3) / 1e9
+        kname = {"link": "link_pass", "stream": "stream_pass"}[dom]
+        kt = {k: round(v, 5) for k, v in kt.items()}
+        roofline = {"bound": "hbm", "kernel": kname, "achieved": round(achieved, 2),
+                    "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
+                    "traffic": load_traffic(kname, passes, args.config), "algorithmic_bytes": bm[dom]}
 
     out_tol = {}
     if not args.no_tol:
@@ -670,13 +675,11 @@ def main():
         "config": {"workload": f"{args.config} (m={inst.m}, n={inst.n}, nnz={inst.nnz})",
                    "m": inst.m, "n": inst.n, "nnz": inst.nnz, "scale": args.scale,
                    "route_len_mean": round(st["route_len_mean"], 4),
-                   "check_every": 10, "adapt_every": 50, "alpha": 1.6, "layout": used},
+                   "check_every": 10, "adapt_every": 50, "alpha": 1.6, "layout": used, "passes": passes},
         "model_gbs": round(bm["iteration"] * ips / 1e9, 2),
         "model_bytes_per_iter": bm["iteration"],
-        "kernel_ms": {k2: round(v, 5) for k2, v in kt.items()},
-        "roofline": {"bound": "hbm", "kernel": kname, "achieved": round(achieved, 2),
-                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": traffic, "algorithmic_bytes": bm[dom]},
+        "kernel_ms": kt,
+        "roofline": roofline,
         "cpu_baseline": cpu,
         "setup_s": round(setup_s, 3),
     }

@@ -270,7 +270,9 @@ pmp_status pmp_history(pmp_handle *h, double *out, int32_t capacity, int32_t *co
  * return average milliseconds in host ms[4]: stream pass and link pass of
  * the other iterations, stream pass and link pass of check iterations (the
  * latter including the check's finalize kernel and, at balancing
- * iterations, the rescale of u); 0 when none ran. */
+ * iterations, the rescale of u); 0 when none ran.  Where pmp_get_passes says
+ * PMP_PASSES_ON_CHIP, pmp_iterate and pmp_solve launch no passes: the gather
+ * passes timed here are those that reverse mode runs. */
 pmp_status pmp_time_kernels(pmp_handle *h, int32_t k, double *ms);
 
 /* Replace the weights w[n] (device memory, problem dtype, > 0), keeping each
@@ -367,8 +369,15 @@ pmp_status pmp_batch_reset(pmp_batch *b);
 pmp_status pmp_batch_profile(pmp_batch *b, double *ms);
 pmp_status pmp_batch_destroy(pmp_batch *b);
 
-/* The layout chosen at setup (PMP_LAYOUT_GATHER or PMP_LAYOUT_BINNED). */
+/* The layout that the sizes ask for (PMP_LAYOUT_GATHER or PMP_LAYOUT_BINNED),
+ * and what the iterations of this instance run: the passes of one of the two,
+ * the passes that gather from LDS, or no passes but whole runs of iterations
+ * on chip (see pmp_params.layout; the choice depends on the pattern too). */
+typedef enum {
+    PMP_PASSES_GATHER = 0, PMP_PASSES_BINNED = 1, PMP_PASSES_STAGED = 2, PMP_PASSES_ON_CHIP = 3
+} pmp_passes;
 pmp_status pmp_get_layout(pmp_handle *h, int32_t *layout);
+pmp_status pmp_get_passes(pmp_handle *h, int32_t *passes);
 
 pmp_status pmp_destroy(pmp_handle *h);
 

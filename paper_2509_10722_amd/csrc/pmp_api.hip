@@ -1459,6 +1459,19 @@ pmp_status pmp_get_layout(pmp_handle *h, int32_t *layout)
     return PMP_OK;
 }
 
+pmp_status pmp_get_passes(pmp_handle *h, int32_t *passes)
+{
+    if (!h || !passes) return fail(PMP_ERR_INVALID, "NULL argument");
+    auto of = [](const auto &d) {
+        return d.resident ? PMP_PASSES_ON_CHIP
+               : d.staged ? PMP_PASSES_STAGED
+               : d.binned ? PMP_PASSES_BINNED
+                          : PMP_PASSES_GATHER;
+    };
+    *passes = h->dtype == PMP_F32 ? of(h->df) : of(h->dd);
+    return PMP_OK;
+}
+
 pmp_status pmp_destroy(pmp_handle *h)
 {
     if (!h) return PMP_OK;

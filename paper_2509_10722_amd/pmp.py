@@ -78,6 +78,7 @@ _SIGNATURES = {
                          ctypes.POINTER(ctypes.c_double)],
     "pmp_backward": [_P, _P, _P],
     "pmp_get_layout": [_P, ctypes.POINTER(ctypes.c_int32)],
+    "pmp_get_passes": [_P, ctypes.POINTER(ctypes.c_int32)],
     "pmp_get_path_prices": [_P, _P],
     "pmp_prune_workspace_size": [_P, ctypes.POINTER(ctypes.c_size_t)],
     "pmp_prune": [_P, _P, _P, ctypes.c_size_t, _P, _P, _P, _P, _P, _P, _P, _P,
@@ -344,8 +345,16 @@ class Solver:
         _check(self.lib.pmp_backward(self.handle, gc.data_ptr(), gw.data_ptr()), "pmp_backward")
         return gc, gw[: self.n]
 
+    def passes_in_use(self):
+        """What the iterations run: 'gather', 'binned' or 'staged' passes, or
+        'on-chip' (whole runs of iterations in one launch, no passes)."""
+        v = ctypes.c_int32()
+        _check(self.lib.pmp_get_passes(self.handle, ctypes.byref(v)), "pmp_get_passes")
+        return ("gather", "binned", "staged", "on-chip")[v.value]
+
     def layout_in_use(self):
-        """'binned' or 'gather': the layout the library chose at setup."""
+        """'binned' or 'gather': the layout that the sizes ask for
+        (passes_in_use says what runs)."""
         v = ctypes.c_int32()
         _check(self.lib.pmp_get_layout(self.handle, ctypes.byref(v)), "pmp_get_layout")
         return "binned" if v.value == PMP_LAYOUT_BINNED else "gather"
