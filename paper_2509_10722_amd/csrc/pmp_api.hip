@@ -511,7 +511,8 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
         if (step > 1 && (size_t)((m + step - 1) / step + 1) > (size_t)L.bp.P * (size_t)L.bp.Q) step = 1;
         pmp_status rs = rows();
         if (rs != PMP_OK) return rs;
-        if (step == 1 || !binned_blocks_sampled(hptr.data(), (int)hptr.size(), step, m, n, nnz, bp, lbs.data(), sbs.data())) {
+        if (step == 1 || !binned_blocks_sampled(hptr.data(), (int)hptr.size(), step, hc.longest_link, m, n, nnz, bp,
+                                                lbs.data(), sbs.data())) {
             if (step > 1) {
                 step = 1;
                 bp = L.bp;

@@ -90,18 +90,39 @@ void binned_blocks(const int *row_ptr, int m, int n, long long nnz, BinnedPlan &
     for (int q = 0; q <= q0; ++q) sbs[q] = (int)std::min<long long>((long long)q * sb0, n);
 }
 
-bool binned_blocks_sampled(const int *samples, int count, int step, int m, int n, long long nnz, BinnedPlan &bp,
-                           int *lbs, int *sbs)
+bool binned_blocks_sampled(const int *samples, int count, int step, int longest, int m, int n, long long nnz,
+                           BinnedPlan &bp, int *lbs, int *sbs)
 {
     const BinnedPlan bound = bp;
     int p0, lb0, q0, sb0;
     count_blocks(m, n, nnz, p0, lb0, q0, sb0);
     const int rows = count - 1, cap = row_cap(lb0) / step;
-    // blocks closed by the cap now number up to rows / cap
-    if (cap < 1 || p0 + (rows + cap - 1) / cap + 1 > bound.P) return false;
-    bp.P = cut_blocks(samples, rows, nnz, p0, cap, lbs, bp.LB);
-    for (int p = 0; p <= bp.P; ++p) lbs[p] = (int)std::min<long long>((long long)lbs[p] * step, m);
-    bp.LB *= step;
+    if (cap < 1) return false;
+    // A block ends at the sample nearest to its quota, and what it has more or
+    // less (up to the half step that this can be) the next one makes up for.
+    // Ending at the first sample past the quota, the half steps add up to a block
+    // too few and a short last one (5e6 links, 511 blocks for two on each CU: the
+    // iterations 1.6% slower).  The cap is a whole number of steps, so blocks
+    // closed by it may number one or two more than the plan allows for from 3e6
+    // links on; few are, and only a cut that does come to more is refused.  So is
+    // one with a block that every row pointer would cut much smaller: several long
+    // rows within a step.
+    const long long quota = std::max<long long>(1, (nnz + p0 - 1) / p0), half = nnz * step / (2LL * m);
+    long long want = quota;
+    int nb = 0, s = 0, most = 0;
+    lbs[0] = 0;
+    for (int i = 1; i <= rows; ++i) {
+        const long long have = (long long)samples[i] - samples[s];
+        if (i == rows || i - s >= cap || (have + half >= want && nnz - samples[i] > half)) {
+            if (nb == bound.P || have > quota + longest + 3 * half) return false;
+            lbs[++nb] = (int)std::min<long long>((long long)i * step, m);
+            most = std::max(most, i - s);
+            s = i;
+            want = quota + std::max(-half, std::min(half, want - have));
+        }
+    }
+    bp.P = nb;
+    bp.LB = most * step;
     bp.Q = q0;
     bp.SB = sb0;
     for (int q = 0; q <= q0; ++q) sbs[q] = (int)std::min<long long>((long long)q * sb0, n);

@@ -289,10 +289,11 @@ BinnedPlan binned_plan(int m, int n, long long nnz);
 // bp to the actual values (within the bounds of binned_plan).
 void binned_blocks(const int *row_ptr, int m, int n, long long nnz, BinnedPlan &bp, int *lbs,
                    int *sbs);
-// The same from every step-th row pointer (count of them, the last one nnz):
-// blocks start at multiples of step.  False where they would exceed the bounds.
-bool binned_blocks_sampled(const int *samples, int count, int step, int m, int n, long long nnz, BinnedPlan &bp,
-                           int *lbs, int *sbs);
+// The same from every step-th row pointer (count of them, the last one nnz) and
+// the longest row: blocks start at multiples of step.  False where they would
+// exceed the bounds or be much less even.
+bool binned_blocks_sampled(const int *samples, int count, int step, int longest, int m, int n, long long nnz,
+                           BinnedPlan &bp, int *lbs, int *sbs);
 // Host construction of ox, ov, lix, six from the CSR pattern and the blocks.
 // With mark_long, lix entries of rows longer than kCap carry kLongBit.
 void binned_build_host(const int *row_ptr, const int *col_idx, int m, int n, const BinnedPlan &bp,

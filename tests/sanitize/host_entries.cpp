@@ -107,8 +107,58 @@ static void check_walks()
         REQUIRE(quads_end((int)e) == (int)((e + 3) / 4));
 }
 
+// Link blocks from sampled row pointers, at the sizes of the large networks:
+// taken, within the plan's bounds (the block starts' array ends there), every
+// row once, and no block much heavier than its share.
+static void check_sampled(int m, int n, long long nnz, int kind, bool taken)
+{
+    std::vector<int> ptr((size_t)m + 1, 0);
+    unsigned long long state = 7;
+    for (int l = 0; l < m; ++l) {
+        state = state * 6364136223846793005ull + 1442695040888963407ull;
+        const long long mean = nnz / m;
+        long long d = 0;
+        if (kind == 0) d = (long long)(state >> 33) % (2 * mean + 1);          // about the mean
+        else if (kind == 1) d = l < m / 2 ? 0 : 2 * mean;                      // half the links unused
+        else d = l % 5000 == 0 ? 4000 : l % 3 == 0 ? mean : 0;                 // hubs among short rows
+        ptr[(size_t)l + 1] = (int)std::min<long long>(nnz, ptr[(size_t)l] + d);
+    }
+    const long long have = ptr[(size_t)m];
+    long long most = 0, longest = 0;
+    for (int l = 0; l < m; ++l) longest = std::max<long long>(longest, ptr[(size_t)l + 1] - ptr[(size_t)l]);
+    const int step = (int)std::max<long long>(1, ((long long)m + 65535) / 65536);
+    std::vector<int> samples;
+    for (long long k = 0; k < m; k += step) samples.push_back(ptr[(size_t)k]);
+    samples.push_back((int)have);
+    const BinnedPlan bound = binned_plan(m, n, have);
+    BinnedPlan bp = bound;
+    std::vector<int> lbs((size_t)bound.P + 1), sbs((size_t)bound.Q + 1);
+    const bool ok = binned_blocks_sampled(samples.data(), (int)samples.size(), step, (int)longest, m, n, have, bp,
+                                          lbs.data(), sbs.data());
+    REQUIRE(ok || !taken);
+    if (!ok) return;
+    REQUIRE(bp.P >= 1 && bp.P <= bound.P && bp.LB <= bound.LB && bp.Q == bound.Q);
+    REQUIRE(lbs[0] == 0 && lbs[(size_t)bp.P] == m);
+    for (int p = 0; p < bp.P; ++p) {
+        REQUIRE(lbs[(size_t)p + 1] > lbs[(size_t)p] && lbs[(size_t)p + 1] - lbs[(size_t)p] <= bp.LB);
+        most = std::max<long long>(most, ptr[(size_t)lbs[(size_t)p + 1]] - ptr[(size_t)lbs[(size_t)p]]);
+    }
+    // at most the longest row and a step and a half of mean rows past the quota
+    const int blocks0 = bound.P - (m + bound.LB - 1) / bound.LB - 1;
+    const long long quota = (have + blocks0 - 1) / blocks0;
+    REQUIRE(most <= quota + longest + 3 * (have * step / (2LL * m)));
+    // even rows: no block too few (the others would carry it), at most one more by the cap
+    if (kind == 0) REQUIRE(bp.P >= blocks0 && bp.P <= blocks0 + 1);
+}
+
 int main()
 {
+    for (int kind = 0; kind < 3; ++kind) {
+        check_sampled(1000000, 500000, 5000000LL, kind, kind == 0);
+        check_sampled(3000000, 3000000, 30000000LL, kind, kind == 0);
+        check_sampled(5000000, 20000000, 117000000LL, kind, kind == 0);
+        check_sampled(10000000, 5000000, 50000000LL, kind, kind == 0);
+    }
     check_walks();
     check_lower_entry();
     check_staged_plan();
