@@ -138,6 +138,9 @@ Layout plan(int m, int n, long long nnz, size_t sz, int layout)
     L.hist = take(sizeof(HistEntry) * kHist);
     L.util = take((size_t)n);
     L.rsync = take(sizeof(ResSync));
+    // An instance runs one of the two: they share their place (the staged tables
+    // are built first; where the pattern is refused, the binned ones overwrite them).
+    const size_t shared = off;
     if (L.binned) {
         const size_t tiles = (size_t)L.bp.P * (size_t)L.bp.Q + 1;
         // 4 entries of padding: the accumulation reads aligned groups of 4
@@ -154,17 +157,19 @@ Layout plan(int m, int n, long long nnz, size_t sz, int layout)
         L.rlen = take((size_t)n);
         L.dlen = take((size_t)m);
     }
+    const size_t binned_end = off;
     if (L.staged) {
+        off = shared;
         L.perm_s = take(staged_slots(L.ss) * 2);
         L.desc_s = take(staged_tiles(L.ss) * sizeof(uint4));
-        L.words_s = take(staged_words_cap(nnz) * 4);
+        L.words_s = take(staged_words_cap(L.ss, nnz) * 4);
         L.perm_l = take(staged_slots(L.sl) * 2);
         L.desc_l = take(staged_tiles(L.sl) * sizeof(uint4));
-        L.words_l = take(staged_words_cap(nnz) * 4);
+        L.words_l = take(staged_words_cap(L.sl, nnz) * 4);
         L.lsum = take((size_t)L.sl.S * m * 8);
         L.st_scratch = take((staged_scratch_ints(L.ss) + staged_scratch_ints(L.sl)) * 4);
     }
-    L.total = off;
+    L.total = std::max(off, binned_end);
     return L;
 }
 

@@ -354,7 +354,7 @@ void launch_resident(const Dev<T> &d, int iters, bool end_check, int ce, int ada
 bool staged_plan(int m, int n, long long nnz, size_t sz, StagedSide &ss, StagedSide &sl);
 size_t staged_tiles(const StagedSide &sd);
 size_t staged_slots(const StagedSide &sd);
-size_t staged_words_cap(long long nnz);
+size_t staged_words_cap(const StagedSide &sd, long long nnz);
 size_t staged_scratch_ints(const StagedSide &sd);
 // One side's pattern (CSC for streams, CSR for links) and the place of its tables.
 struct StagedTables {

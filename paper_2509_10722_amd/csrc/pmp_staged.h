@@ -492,7 +492,13 @@ bool staged_plan(int m, int n, long long nnz, size_t sz, StagedSide &ss, StagedS
 
 size_t staged_tiles(const StagedSide &sd) { return (size_t)sd.R * sd.C * kSW; }
 size_t staged_slots(const StagedSide &sd) { return (size_t)sd.R * sd.C * kStK * kST; }
-size_t staged_words_cap(long long nnz) { return 2 * (size_t)nnz + 65536; }
+// Index words a side may take.  A tile needs at most a word an entry, and a slice
+// of its widest row (64 lanes, at most 64 words): every other slice is no wider
+// than the rows of the one before it.
+size_t staged_words_cap(const StagedSide &sd, long long nnz)
+{
+    return std::min(2 * (size_t)nnz + 65536, (size_t)nnz + (size_t)sd.R * sd.C * 64 * 64);
+}
 size_t staged_scratch_ints(const StagedSide &sd)
 {
     return 2 * staged_tiles(sd) + 2 + scan_scratch_ints((int)staged_tiles(sd));
@@ -520,7 +526,7 @@ hipError_t staged_build(StagedSide &ss, const StagedTables &ts, StagedSide &sl, 
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
     *ok = true;
-    for (int k = 0; k < 2; ++k) *ok = *ok && h[k][1] == 0 && h[k][0] >= 0 && (size_t)h[k][0] * 64 <= staged_words_cap(nnz);
+    for (int k = 0; k < 2; ++k) *ok = *ok && h[k][1] == 0 && h[k][0] >= 0 && (size_t)h[k][0] * 64 <= staged_words_cap(*sd[k], nnz);
     if (!*ok) return hipSuccess;
     for (int k = 0; k < 2; ++k) {
         hipLaunchKernelGGL(k_staged_fill, dim3(sd[k]->R * sd[k]->C), dim3(kST), 0, s, *sd[k], tb[k]->ptr, tb[k]->idx,

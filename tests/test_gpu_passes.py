@@ -85,6 +85,21 @@ def test_staged_of_binned_size_equals_both():
     a.close()
 
 
+def test_refused_tables_leave_the_binned_layout_whole():
+    """The staged tables are built where the binned ones go when the pattern is
+    too uneven for them."""
+    inst = _staged_instance(20000, 300000, 5, 11, 3900)
+    assert inst.nnz >= 2 ** 21
+    a, b = Solver(inst), Solver(inst, layout=PMP_LAYOUT_GATHER)
+    assert a.passes_in_use() == "binned" and b.passes_in_use() == "gather"
+    for s in (a, b):
+        s.iterate(57)
+    for k in ("x", "a", "b", "zs", "u"):
+        assert torch.equal(a.views()[k], b.views()[k]), k
+    a.close()
+    b.close()
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
 @pytest.mark.parametrize("rel", [0.0, 1e-3])
 def test_staged_solve_stops_and_balances_like_gather(rel, dtype):
