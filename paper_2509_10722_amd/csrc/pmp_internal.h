@@ -20,16 +20,18 @@ constexpr int kBlock = 256;
 constexpr int kCap = 4096;
 // Problems whose nonzeros fill fewer than kSmallBlocks workgroups of kCap (one
 // per CU) are cut into smaller ones, about kBlockTarget of them with at least
-// 64 segments and 1,024 nonzeros allowed, so that a small pass still spreads
-// over the chip.  Measured (MI355X, both passes): 50,000 streams on 1,000 links,
-// nnz = 4e5, 17.9 -> 12.6 us; 1e5 streams on 1e4 links, nnz = 7.5e5, 14.4 -> 12.9 us.
+// 128 segments and 1,024 nonzeros allowed, so that a small pass still spreads
+// over the chip.  Measured (MI355X, both passes, against full blocks): 50,000
+// streams on 1,000 links, nnz = 4e5, 13.3 -> 13.0 us; 1e5 streams on 1e4 links,
+// nnz = 7.5e5, 14.5 -> 13.7; 60,000 on 60,000, nnz = 3.3e5, 11.8 -> 11.4, where 64
+// segments took 12.6.
 constexpr int kSmallBlocks = 256;
 constexpr int kBlockTarget = 1024;
 inline bool small_blocks(long long nnz) { return nnz < (long long)kSmallBlocks * kCap; }
 inline int block_segments(long long count, long long nnz)
 {
     if (!small_blocks(nnz)) return kBlock;
-    return (int)std::min<long long>(kBlock, std::max<long long>(64, (count / kBlockTarget + 63) / 64 * 64));
+    return (int)std::min<long long>(kBlock, std::max<long long>(128, (count / kBlockTarget + 63) / 64 * 64));
 }
 inline int block_nonzeros(long long nnz)
 {

@@ -151,8 +151,21 @@ static void check_sampled(int m, int n, long long nnz, int kind, bool taken)
     if (kind == 0) REQUIRE(bp.P >= blocks0 && bp.P <= blocks0 + 1);
 }
 
+// Workgroups of the gather passes over small problems: never so few segments
+// that there are more of them than the chip takes at once for nothing.
+static void check_small_blocks()
+{
+    for (long long nnz : {1000LL, 330000LL, 750000LL, (1LL << 20) - 1, 1LL << 20, 1LL << 30})
+        for (int count : {1, 1000, 19800, 60000, 200000, 1000000, 2000000000}) {
+            const int segs = block_segments(count, nnz), cap = block_nonzeros(nnz);
+            REQUIRE(segs >= 128 && segs <= kBlock && segs % 64 == 0 && cap >= 1024 && cap <= kCap);
+            if (!small_blocks(nnz)) REQUIRE(segs == kBlock && cap == kCap);
+        }
+}
+
 int main()
 {
+    check_small_blocks();
     for (int kind = 0; kind < 3; ++kind) {
         check_sampled(1000000, 500000, 5000000LL, kind, kind == 0);
         check_sampled(3000000, 3000000, 30000000LL, kind, kind == 0);
