@@ -291,7 +291,9 @@ pmp_status pmp_update_weights(pmp_handle *h, const void *w_new);
  * aligned, which must stay valid until pmp_backward); the backward pass
  * recomputes each segment of s iterations, records x and the slack-prox mask,
  * and runs the reverse iteration.  Afterwards the handle holds the state of
- * iteration K again. */
+ * iteration K again.  The sums of the reverse iteration are formed in FP64; their
+ * terms are FP64 too, except for FP32 problems whose layout (pmp_get_layout) is
+ * PMP_LAYOUT_BINNED, which hold them in FP32 as they do the forward messages. */
 pmp_status pmp_adjoint_workspace_size(pmp_handle *h, int32_t K, int32_t s, size_t *bytes);
 /* Run K iterations with checkpoints every s; J (host) receives the objective. */
 pmp_status pmp_forward_ckpt(pmp_handle *h, int32_t K, int32_t s, void *adj_workspace,

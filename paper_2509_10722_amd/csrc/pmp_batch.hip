@@ -358,7 +358,7 @@ __device__ __forceinline__ void link_tile(const BDev<T> &d, int tile, T *sx, dou
     if (ck.y > 0) {
         last = link_chunk<T, MODE>(d, di, inst, tile, ck.x, ck.y, sred, r2, s2);
     } else {
-        // at most kCap nonzeros: rows longer than that are chunk tiles
+        // at most kBS entries, and no row of more than kCap: those are chunk tiles
         const int l0 = d.lt_seg[tile], l1 = d.lt_seg[tile + 1];
         const int e0 = di.row_ptr[l0];
         const int cnt = di.row_ptr[l1] - e0;

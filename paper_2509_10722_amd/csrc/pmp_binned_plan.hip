@@ -29,15 +29,18 @@ void split_by_count(int count, int groups, int &blocks, int &size)
 // average, so that two workgroups share each CU: measured on MI355X, +9% to
 // +13% at 2.5e7 to 6e7 nonzeros.  Where both sides have 256 blocks, both
 // passes run their one-workgroup form (pmp_binned.hip), which is the faster up
-// to about 1.3e7 nonzeros (an iteration at 9e6: 51.8 us against 57.8, at
-// 1.2e7: 61.0 against 67.6, at 1.5e7: 87.9 against 86.7).
+// to about 1.3e7 nonzeros, so neither side is doubled before 200 nonzeros a tile.
+// An iteration with 256 blocks a side, with 512 on the stream side, with 512 on
+// both: 1.8e6 links x 9e5 streams, nnz = 9e6, 54.3, 59.5, 61.6 us; 1e6 x 1e6, 1.2e7,
+// 60.3, 65.8, 67.0; 3e5 x 1e6, 9e6, 50.0, 55.0, 55.1; 1e5 x 5e5 with 100 links on
+// 50,000 streams, 1e7, 94, 107, 115; at 1.5e7, 87.9 and 86.7 (512 on the link side).
 void count_blocks(int m, int n, long long nnz, int &p0, int &lb0, int &q0, int &sb0)
 {
     split_by_count(m, 1, p0, lb0);
     split_by_count(n, 1, q0, sb0);
-    const long long tile = p0 < 512 && q0 < 512 ? 200 : 64 * 2;
-    if (p0 < 512 && m >= 512 && nnz >= tile * p0 * q0) split_by_count(m, 2, p0, lb0);
-    if (q0 < 512 && n >= 512 && nnz >= 64LL * p0 * 2 * q0) split_by_count(n, 2, q0, sb0);
+    auto tile = [&] { return m >= 512 && p0 < 512 && q0 < 512 ? 200LL : 64LL * 2; };
+    if (p0 < 512 && m >= 512 && nnz >= tile() * p0 * q0) split_by_count(m, 2, p0, lb0);
+    if (q0 < 512 && n >= 512 && nnz >= tile() * p0 * q0) split_by_count(n, 2, q0, sb0);
 }
 
 // Row cap of a balanced block: a quarter above the count-based size, within

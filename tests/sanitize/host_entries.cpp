@@ -163,8 +163,24 @@ static void check_small_blocks()
         }
 }
 
+// Up to 200 nonzeros a tile of 256 x 256 blocks, neither side of a problem has
+// more (bp.Q is the stream blocks; bp.P bounds the link blocks from above).
+static void check_block_counts()
+{
+    const long long line = 200LL * 256 * 256;
+    const int sizes[][2] = {{1000000, 800000}, {1800000, 900000}, {300000, 1000000}, {100000, 500000}};
+    for (auto &z : sizes)
+        for (long long nnz : {2200000LL, 5000000LL, 8400000LL, 9000000LL, 12000000LL, line - 300000, line + 300000, 3 * line}) {
+            const BinnedPlan bp = binned_plan(z[0], z[1], nnz);
+            const int blocks0 = bp.P - (z[0] + bp.LB - 1) / bp.LB - 1;
+            const bool one = nnz < line - 200000;        // (a few blocks less than 256 by rounding)
+            REQUIRE(one ? bp.Q <= 256 && blocks0 <= 256 : blocks0 > 256);
+        }
+}
+
 int main()
 {
+    check_block_counts();
     check_small_blocks();
     for (int kind = 0; kind < 3; ++kind) {
         check_sampled(1000000, 500000, 5000000LL, kind, kind == 0);
