@@ -449,7 +449,7 @@ constexpr int kRawBuffer = 0x00027000;      // resource word 3: 32-bit data, bou
 
 // Adds the entries [e0, e1) as accumulate does.  The indices go to cache,
 // from entry e0 & ~3 on, where cache is given.
-template <typename T, bool RUNS>
+template <typename T, bool RUNS, bool FX>
 struct OneEntries {
     static constexpr int K = sizeof(T) == 4 ? kOneQuads : 4;
     typedef T v4 __attribute__((ext_vector_type(4)));
@@ -477,7 +477,8 @@ struct OneEntries {
             k[g] = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b64(x, b * 8, 0, kNt));
         }
     }
-    __device__ __forceinline__ void add(const T *msg, const uint16_t *idx, int e0, int e1, acc_t *acc, u4 *cache)
+    __device__ __forceinline__ void add(const T *msg, const uint16_t *idx, int e0, int e1, acc_t *acc, u4 *cache,
+                                        double fxs)
     {
         const int lane = threadIdx.x & 63, q0 = e0 >> 2, b1 = quads_end(e1);
         int w = q0 + (threadIdx.x & ~63);
@@ -486,25 +487,25 @@ struct OneEntries {
             if (w < b1) {                                  // the whole wave
                 const int b = w + lane;
                 if (cache && b < b1) cache[b - q0] = k[g];
-                add_quad<RUNS, false>(v[g], k[g], b << 2, e0, e1, b < b1, acc, 0.0);
+                add_quad<RUNS, FX>(v[g], k[g], b << 2, e0, e1, b < b1, acc, fxs);
             }
         for (; w < b1; w += kBinThreads) {
             const int b = w + lane, bc = min(b, b1 - 1);
             const v4 x = __builtin_nontemporal_load((const v4 *)msg + bc);
             const u4 y = __builtin_nontemporal_load((const u4 *)idx + bc);
             if (cache && b < b1) cache[b - q0] = y;
-            add_quad<RUNS, false>(x, y, b << 2, e0, e1, b < b1, acc, 0.0);
+            add_quad<RUNS, FX>(x, y, b << 2, e0, e1, b < b1, acc, fxs);
         }
     }
 };
 
 // emit_tiles with the offsets in registers and the indices read through at(e).
-template <typename T, bool NT, typename At>
+template <typename T, bool LONG, bool NT, typename At>
 __device__ __forceinline__ void one_emit(const OneTiles &o, const acc_t *vals, T *__restrict__ out, At at)
 {
     constexpr int U = PMP_BIN_EMIT_U;
     auto put = [&](int at, int i) {
-        const T x = (T)vals[i];
+        const T x = (T)vals[LONG ? i & kLocalMask : i];
         if (NT) __builtin_nontemporal_store(x, out + at);
         else out[at] = x;
     };
@@ -619,14 +620,14 @@ PMP_BIN_ONE_KERNEL void k_bin_stream_one(Dev<T> d, int cap, int nt)
     uint16_t *kept = (uint16_t *)(S + d.SB);
     const bool fits = quads_end(e1) - (e0 >> 2) <= cap / 4;
     constexpr int G = kOneStreams;
-    OneEntries<T, false> en;
+    OneEntries<T, false, false> en;
     OneStreams<T, MODE, G> rows;
     OneTiles tl;
     en.load(d.mv, d.six, e0, e1);
     tl.load(ov, d.oxq + (long long)q * d.P, d.P);
     for (int i = threadIdx.x; i < j1 - j0; i += kBinThreads) S[i] = 0.0;
     __syncthreads();
-    en.add(d.mv, d.six, e0, e1, S, fits ? (u4 *)kept : nullptr);
+    en.add(d.mv, d.six, e0, e1, S, fits ? (u4 *)kept : nullptr, 0.0);
     rows.load(d, j0, j1);
     __syncthreads();
     double part = 0.0;
@@ -654,16 +655,16 @@ PMP_BIN_ONE_KERNEL void k_bin_stream_one(Dev<T> d, int cap, int nt)
     }
     __syncthreads();
     auto at = [&](int e) { return kept[e - (e0 & ~3)]; };
-    if (!fits) one_emit<T, false>(tl, S, d.mx, [&](int e) { return d.six[e]; });
-    else if (nt) one_emit<T, true>(tl, S, d.mx, at);
-    else one_emit<T, false>(tl, S, d.mx, at);
+    if (!fits) one_emit<T, false, false>(tl, S, d.mx, [&](int e) { return d.six[e]; });
+    else if (nt) one_emit<T, false, true>(tl, S, d.mx, at);
+    else one_emit<T, false, false>(tl, S, d.mx, at);
     if (MODE == kCheck) {
         part = block_sum_n<kBinThreads>(part, sred);
         if (threadIdx.x == 0) d.spart[q] = part;
     }
 }
 
-template <typename T, int MODE>
+template <typename T, int MODE, bool FX>
 PMP_BIN_ONE_KERNEL void k_bin_link_one(Dev<T> d, int cap, int nt)
 {
     typedef unsigned short u4 __attribute__((ext_vector_type(4)));
@@ -680,14 +681,14 @@ PMP_BIN_ONE_KERNEL void k_bin_link_one(Dev<T> d, int cap, int nt)
     uint16_t *kept = (uint16_t *)(Y + d.LB);
     const bool fits = quads_end(e1) - (e0 >> 2) <= cap / 4;
     constexpr int G = MODE == kCheck || sizeof(T) == 8 ? 2 : kOneLinks;   // a check carries more inputs
-    OneEntries<T, sizeof(T) == 4 && PMP_BIN_RUNS> en;
+    OneEntries<T, sizeof(T) == 4 && PMP_BIN_RUNS, FX> en;
     OneLinks<T, MODE, G> rows;
     OneTiles tl;
     en.load(d.mx, d.lix, e0, e1);
     tl.load(ox, d.ovp + (long long)p * d.Q, d.Q);
     for (int i = threadIdx.x; i < l1 - l0; i += kBinThreads) Y[i] = 0.0;
     __syncthreads();
-    en.add(d.mx, d.lix, e0, e1, Y, fits ? (u4 *)kept : nullptr);
+    en.add(d.mx, d.lix, e0, e1, Y, fits ? (u4 *)kept : nullptr, d.fx_scale);
     rows.load(d, l0, l1);
     __syncthreads();
     double r2 = 0.0, s2 = 0.0;
@@ -701,7 +702,8 @@ PMP_BIN_ONE_KERNEL void k_bin_link_one(Dev<T> d, int cap, int nt)
                 const int deg = rows.g1[g] - rows.g0[g];
                 const LinkIn in{(double)rows.c[g], (double)rows.u[g], (double)rows.b[g], (double)rows.zs[g],
                                 MODE == kCheck ? rows.yp[g] : 0.0, MODE == kCheck ? rows.pp[g] : 0.0};
-                const double y = (double)Y[l - l0];
+                double y = (double)Y[l - l0];
+                if (FX && deg > kCap) y = (double)__double_as_longlong(Y[l - l0]) * d.fx_inv;
                 // v goes out in the messages; a check also stores it
                 Y[l - l0] = (acc_t)link_update_in<T, MODE, MODE == kCheck>(d, l, deg, y, in, r2, s2);
             }
@@ -717,9 +719,9 @@ PMP_BIN_ONE_KERNEL void k_bin_link_one(Dev<T> d, int cap, int nt)
     }
     __syncthreads();
     auto at = [&](int e) { return kept[e - (e0 & ~3)]; };
-    if (!fits) one_emit<T, false>(tl, Y, d.mv, [&](int e) { return d.lix[e]; });
-    else if (nt) one_emit<T, true>(tl, Y, d.mv, at);
-    else one_emit<T, false>(tl, Y, d.mv, at);
+    if (!fits) one_emit<T, FX, false>(tl, Y, d.mv, [&](int e) { return d.lix[e]; });
+    else if (nt) one_emit<T, FX, true>(tl, Y, d.mv, at);
+    else one_emit<T, FX, false>(tl, Y, d.mv, at);
 }
 
 // After a check (apply = 1): apply a pending u rescale (eq. (18)), refresh
@@ -865,9 +867,10 @@ void binned_configure()
     PMP_BIN_ATTR((k_bin_adj_emit<float>));
     PMP_BIN_ATTR((k_bin_adj_emit<double>));
     auto one = [&](const void *f) { (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kOneLds); };
-#define PMP_BIN_ONE_ATTR(T, MODE)                   \
-    one((const void *)(k_bin_stream_one<T, MODE>)); \
-    one((const void *)(k_bin_link_one<T, MODE>));
+#define PMP_BIN_ONE_ATTR(T, MODE)                        \
+    one((const void *)(k_bin_stream_one<T, MODE>));      \
+    one((const void *)(k_bin_link_one<T, MODE, false>)); \
+    one((const void *)(k_bin_link_one<T, MODE, sizeof(T) == 4>));
     PMP_BIN_ONE_ATTR(float, kPlain)
     PMP_BIN_ONE_ATTR(float, kSave)
     PMP_BIN_ONE_ATTR(float, kCheck)
@@ -878,11 +881,7 @@ void binned_configure()
 #undef PMP_BIN_ATTR
 }
 
-// A side whose blocks all have a CU of their own takes the passes above, but not
-// a link side with long rows: its largest blocks hold several times the entries
-// that are loaded at once, and the rest come a round at a time (100,000 links x
-// 500,000 streams, 30 links on 50,000 streams each, nnz = 6.5e6: 95.7 us an
-// iteration against 86.2, in FP64 130 against 119).  The
+// A side whose blocks all have a CU of their own takes the passes above; the
 // indices of cap entries stay in LDS (a quarter more than the mean, in what one
 // workgroup may have).  With several blocks a CU, two resident workgroups
 // overlap their phases instead: 2e7 nonzeros 106 us against 111, 4e7 210
@@ -930,16 +929,23 @@ void launch_bin_stream(const Dev<T> &d, int mode, hipStream_t s)
     }
 }
 
+template <typename T, bool FX>
+void launch_bin_link_one(const Dev<T> &d, int mode, int cap, int nt, size_t lds, hipStream_t s)
+{
+    const dim3 g(d.P), b(kBinThreads);
+    if (mode == kPlain) hipLaunchKernelGGL((k_bin_link_one<T, kPlain, FX>), g, b, lds, s, d, cap, nt);
+    else if (mode == kSave) hipLaunchKernelGGL((k_bin_link_one<T, kSave, FX>), g, b, lds, s, d, cap, nt);
+    else hipLaunchKernelGGL((k_bin_link_one<T, kCheck, FX>), g, b, lds, s, d, cap, nt);
+}
+
 template <typename T>
 void launch_bin_link(const Dev<T> &d, int mode, hipStream_t s)
 {
     size_t lds = (size_t)d.LB * sizeof(acc_t);
     int cap, nt;
-    if (!d.long_rows && one_block(d, d.P, d.Q, d.LB, cap, nt, lds)) {
-        const dim3 g(d.P), b(kBinThreads);
-        if (mode == kPlain) hipLaunchKernelGGL((k_bin_link_one<T, kPlain>), g, b, lds, s, d, cap, nt);
-        else if (mode == kSave) hipLaunchKernelGGL((k_bin_link_one<T, kSave>), g, b, lds, s, d, cap, nt);
-        else hipLaunchKernelGGL((k_bin_link_one<T, kCheck>), g, b, lds, s, d, cap, nt);
+    if (one_block(d, d.P, d.Q, d.LB, cap, nt, lds)) {
+        if (sizeof(T) == 4 && d.fx_shift) launch_bin_link_one<T, sizeof(T) == 4>(d, mode, cap, nt, lds, s);
+        else launch_bin_link_one<T, false>(d, mode, cap, nt, lds, s);
         return;
     }
     switch (mode) {

@@ -194,7 +194,6 @@ struct Dev {
     int P, Q, LB, SB;
     int SR;                         // stream blocks per dispatch round of the stream pass
     int CUs;                        // compute units of the device (binned layout)
-    int long_rows;                  // some row has more than kCap nonzeros (binned layout)
     const int *lbs, *sbs;           // [P+1], [Q+1] first link / stream of each block
     const uint8_t *rlen;            // [n] route lengths when all are below 256, else NULL
     const uint8_t *dlen;            // [m] link degrees when all are below 256, else NULL
