@@ -542,6 +542,7 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
             HIP_TRY(hipGetDevice(&dev));
             HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
             d.CUs = cus;
+            d.fullest = bp.fullest;
             d.SR = d.Q <= 2 * cus ? std::max(1, d.Q) : std::max(8, cus);
         }
         d.lbs = (const int *)(ws + L.lbs);

@@ -881,7 +881,12 @@ void binned_configure()
 #undef PMP_BIN_ATTR
 }
 
-// A side whose blocks all have a CU of their own takes the passes above; the
+// A side whose blocks all have a CU of their own takes the passes above, but not
+// a link side whose fullest block (long rows) has more entries than are loaded at
+// once and one and a half times the mean: the rest come a round at a time.
+// 1e5 links x 5e5 streams, 30 links on 50,000 streams each, nnz = 6.5e6 (fullest
+// 2.5 times the mean): 95.7 us an iteration against 86.2, in FP64 130 against 119;
+// 1e6 x 5e5, 500 links on 5,000 each, 7.5e6 (1.2 times): 60.0 against 66.5.  The
 // indices of cap entries stay in LDS (a quarter more than the mean, in what one
 // workgroup may have).  With several blocks a CU, two resident workgroups
 // overlap their phases instead: 2e7 nonzeros 106 us against 111, 4e7 210
@@ -943,7 +948,8 @@ void launch_bin_link(const Dev<T> &d, int mode, hipStream_t s)
 {
     size_t lds = (size_t)d.LB * sizeof(acc_t);
     int cap, nt;
-    if (one_block(d, d.P, d.Q, d.LB, cap, nt, lds)) {
+    const bool even = d.fullest <= 4 * kOneQuads * kBinThreads || 2 * (long long)d.fullest * d.P <= 3 * d.nnz;
+    if (even && one_block(d, d.P, d.Q, d.LB, cap, nt, lds)) {
         if (sizeof(T) == 4 && d.fx_shift) launch_bin_link_one<T, sizeof(T) == 4>(d, mode, cap, nt, lds, s);
         else launch_bin_link_one<T, false>(d, mode, cap, nt, lds, s);
         return;

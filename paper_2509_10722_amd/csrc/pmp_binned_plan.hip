@@ -51,16 +51,17 @@ int row_cap(int size) { return std::min(kBinMaxBlock, size + (size + 3) / 4); }
 // by the quota number at most nnz / quota, blocks closed by the cap at most
 // count / cap, so there are at most blocks0 + count / cap + 1 of them.
 int cut_blocks(const int *ptr, int count, long long nnz, int blocks0, int cap, int *starts,
-               int &most)
+               int &most, int &fullest)
 {
     const long long quota = std::max<long long>(1, (nnz + blocks0 - 1) / blocks0);
     int nb = 0, s = 0;
-    most = 0;
+    most = fullest = 0;
     starts[0] = 0;
     for (int i = 1; i <= count; ++i)
         if (i == count || i - s >= cap || (long long)ptr[i] - ptr[s] >= quota) {
             starts[++nb] = i;
             most = std::max(most, i - s);
+            fullest = std::max(fullest, ptr[i] - ptr[s]);
             s = i;
         }
     return nb;
@@ -86,7 +87,7 @@ void binned_blocks(const int *row_ptr, int m, int n, long long nnz, BinnedPlan &
     int p0, lb0, q0, sb0;
     count_blocks(m, n, nnz, p0, lb0, q0, sb0);
     // links: balanced by nonzeros (a congested link has thousands)
-    bp.P = cut_blocks(row_ptr, m, nnz, p0, row_cap(lb0), lbs, bp.LB);
+    bp.P = cut_blocks(row_ptr, m, nnz, p0, row_cap(lb0), lbs, bp.LB, bp.fullest);
     // streams: by count (routes are short), so the block of stream j is j / SB
     bp.Q = q0;
     bp.SB = sb0;
@@ -112,7 +113,7 @@ bool binned_blocks_sampled(const int *samples, int count, int step, int longest,
     // rows within a step.
     const long long quota = std::max<long long>(1, (nnz + p0 - 1) / p0), half = nnz * step / (2LL * m);
     long long want = quota;
-    int nb = 0, s = 0, most = 0;
+    int nb = 0, s = 0, most = 0, fullest = 0;
     lbs[0] = 0;
     for (int i = 1; i <= rows; ++i) {
         const long long have = (long long)samples[i] - samples[s];
@@ -120,12 +121,14 @@ bool binned_blocks_sampled(const int *samples, int count, int step, int longest,
             if (nb == bound.P || have > quota + longest + 3 * half) return false;
             lbs[++nb] = (int)std::min<long long>((long long)i * step, m);
             most = std::max(most, i - s);
+            fullest = std::max(fullest, (int)have);
             s = i;
             want = quota + std::max(-half, std::min(half, want - have));
         }
     }
     bp.P = nb;
     bp.LB = most * step;
+    bp.fullest = fullest;
     bp.Q = q0;
     bp.SB = sb0;
     for (int q = 0; q <= q0; ++q) sbs[q] = (int)std::min<long long>((long long)q * sb0, n);

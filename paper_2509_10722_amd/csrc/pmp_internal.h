@@ -194,6 +194,7 @@ struct Dev {
     int P, Q, LB, SB;
     int SR;                         // stream blocks per dispatch round of the stream pass
     int CUs;                        // compute units of the device (binned layout)
+    int fullest;                    // most nonzeros of a link block (binned layout)
     const int *lbs, *sbs;           // [P+1], [Q+1] first link / stream of each block
     const uint8_t *rlen;            // [n] route lengths when all are below 256, else NULL
     const uint8_t *dlen;            // [m] link degrees when all are below 256, else NULL
@@ -282,6 +283,7 @@ static_assert(kBinMaxBlock <= kLocalMask, "local indices must leave the top bit 
 struct BinnedPlan {
     int P, Q;     // link blocks, stream blocks
     int LB, SB;   // most links / streams in one block (LDS sums per workgroup)
+    int fullest;  // most nonzeros of a link block (0 in the bounds)
 };
 // Bounds of the plan from the sizes alone (workspace sizing).
 BinnedPlan binned_plan(int m, int n, long long nnz);
