@@ -143,12 +143,13 @@ static void check_sampled(int m, int n, long long nnz, int kind, bool taken)
         REQUIRE(lbs[(size_t)p + 1] > lbs[(size_t)p] && lbs[(size_t)p + 1] - lbs[(size_t)p] <= bp.LB);
         most = std::max<long long>(most, ptr[(size_t)lbs[(size_t)p + 1]] - ptr[(size_t)lbs[(size_t)p]]);
     }
-    // at most the longest row and a step and a half of mean rows past the quota
+    // at most the longest row and a step and a half of mean rows past the quota,
+    // which is an eighth above the share at most
     const int blocks0 = bound.P - (m + bound.LB - 1) / bound.LB - 1;
     const long long quota = (have + blocks0 - 1) / blocks0;
-    REQUIRE(most <= quota + longest + 3 * (have * step / (2LL * m)));
-    // even rows: no block too few (the others would carry it), at most one more by the cap
-    if (kind == 0) REQUIRE(bp.P >= blocks0 && bp.P <= blocks0 + 1);
+    REQUIRE(bp.fullest == most && most <= quota + quota / 8 + longest + 3 * (have * step / (2LL * m)));
+    // even rows: the blocks of a multiple of the CUs, or up to a hundredth fewer
+    if (kind == 0) REQUIRE(bp.P <= blocks0 && bp.P >= blocks0 - blocks0 / 100);
 }
 
 // Workgroups of the gather passes over small problems: never so few segments
@@ -178,8 +179,36 @@ static void check_block_counts()
         }
 }
 
+// Every row pointer: rows of which some are empty for a stretch, or much longer
+// than the rest, come to no more blocks than CUs where a little more per block
+// avoids it.
+static void check_even_cut()
+{
+    for (int kind = 0; kind < 3; ++kind) {
+        const int m = 60000, n = 500000;
+        std::vector<int> ptr((size_t)m + 1, 0);
+        for (int l = 0; l < m; ++l) {
+            const int d = kind == 0 ? 60 : kind == 1 ? (l > 29000 && l < 29400 ? 0 : 60) : (l % 1000 == 0 ? 1500 : 50 + l % 7);
+            ptr[(size_t)l + 1] = ptr[(size_t)l] + d;
+        }
+        const long long nnz = ptr[(size_t)m];
+        const BinnedPlan bound = binned_plan(m, n, nnz);
+        BinnedPlan bp = bound;
+        std::vector<int> lbs((size_t)bound.P + 1), sbs((size_t)bound.Q + 1);
+        binned_blocks(ptr.data(), m, n, nnz, bp, lbs.data(), sbs.data());
+        REQUIRE(bp.P <= 256 && bp.P <= bound.P && bp.LB <= bound.LB);
+        long long most = 0;
+        for (int p = 0; p < bp.P; ++p) {
+            REQUIRE(lbs[(size_t)p + 1] > lbs[(size_t)p] && lbs[(size_t)p + 1] - lbs[(size_t)p] <= bp.LB);
+            most = std::max<long long>(most, ptr[(size_t)lbs[(size_t)p + 1]] - ptr[(size_t)lbs[(size_t)p]]);
+        }
+        REQUIRE(lbs[(size_t)bp.P] == m && bp.fullest == most);
+    }
+}
+
 int main()
 {
+    check_even_cut();
     check_block_counts();
     check_small_blocks();
     for (int kind = 0; kind < 3; ++kind) {
