@@ -497,9 +497,7 @@ pmp_status setup_impl(pmp_handle *h, const pmp_problem *p, char *ws)
         // offsets and local indices of the binned message layout
         BinnedPlan bp = L.bp;
         std::vector<int> lbs((size_t)L.bp.P + 1), sbs((size_t)L.bp.Q + 1);
-        // from every step-th row pointer (all of them below 2^16 rows): a link
-        // block then ends at most step rows late, under 1% of its rows
-        int step = (int)std::max<long long>(1, ((long long)m + 65535) / 65536);
+        int step = binned_sample_step(m, n, nnz);
         std::vector<int> hptr;
         auto rows = [&]() -> pmp_status {
             const int count = (int)(((long long)m + step - 1) / step) + 1;

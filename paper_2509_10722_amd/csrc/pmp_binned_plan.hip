@@ -72,16 +72,16 @@ Cut cut_rows(const int *ptr, int count, long long quota, int cap, int *starts)
 }
 
 // The cut at the blocks' share of the nonzeros, or, where rows that are long or
-// empty make that more than blocks0 blocks (a multiple of the CUs), at up to an
-// eighth more if that brings them back: one block too many shares a CU with
-// another for the whole pass.  1.7e5 links x 1.5e6 streams, nnz = 1.2e7, link pass:
+// empty make that more blocks than the CUs hold at once (256, or 512 two a CU),
+// at up to an eighth more if that brings them back: one block too many shares a CU
+// with another for the whole pass, or runs after all others.  1.7e5 links x 1.5e6 streams, nnz = 1.2e7, link pass:
 // 51 us with 257 blocks, 33 with 256.
 template <typename F>
 Cut cut_evenly(long long nnz, int blocks0, F cut)
 {
     const long long quota = std::max<long long>(1, (nnz + blocks0 - 1) / blocks0);
     const Cut plain = cut(quota);
-    if (plain.nb <= blocks0) return plain;
+    if (plain.nb <= blocks0 || blocks0 > 512) return plain;
     for (int k = 128; k >= 8; k /= 2) {
         const Cut c = cut(quota + std::max<long long>(1, quota / k));
         if (c.nb >= 0 && c.nb <= blocks0) return c;
@@ -117,6 +117,16 @@ void binned_blocks(const int *row_ptr, int m, int n, long long nnz, BinnedPlan &
     bp.Q = q0;
     bp.SB = sb0;
     for (int q = 0; q <= q0; ++q) sbs[q] = (int)std::min<long long>((long long)q * sb0, n);
+}
+
+// Up to 2^16 rows all of them; above, so many that a step is at most 1 / 256 of a
+// block's rows (6e6 links: with 1 / 85, iterations 1% slower than with every
+// pointer).
+int binned_sample_step(int m, int n, long long nnz)
+{
+    int p0, lb0, q0, sb0;
+    count_blocks(m, n, nnz, p0, lb0, q0, sb0);
+    return std::max(1, std::min((m + 65535) / 65536, lb0 / 256));
 }
 
 bool binned_blocks_sampled(const int *samples, int count, int step, int longest, int m, int n, long long nnz,

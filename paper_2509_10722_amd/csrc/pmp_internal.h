@@ -293,6 +293,8 @@ BinnedPlan binned_plan(int m, int n, long long nnz);
 // bp to the actual values (within the bounds of binned_plan).
 void binned_blocks(const int *row_ptr, int m, int n, long long nnz, BinnedPlan &bp, int *lbs,
                    int *sbs);
+// Every how many rows a pointer is enough to cut the links by (1: all of them).
+int binned_sample_step(int m, int n, long long nnz);
 // The same from every step-th row pointer (count of them, the last one nnz) and
 // the longest row: blocks start at multiples of step.  False where they would
 // exceed the bounds or be much less even.
