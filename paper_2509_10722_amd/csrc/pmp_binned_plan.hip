@@ -20,8 +20,8 @@ void split_by_count(int count, int groups, int &blocks, int &size)
     const long long per = 256LL * kBinMaxBlock;
     const long long k = std::max<long long>(groups, (count + per - 1) / per);
     blocks = (int)(256 * k);
-    size = (int)std::max<long long>(1, (count + blocks - 1) / blocks);
-    blocks = (int)std::max<long long>(1, (count + size - 1) / size);
+    size = (int)std::max<long long>(1, (count + (long long)blocks - 1) / blocks);
+    blocks = (int)std::max<long long>(1, (count + (long long)size - 1) / size);
 }
 
 // Blocks of both sides.  A side with fewer than 512 blocks (one workgroup
@@ -126,7 +126,7 @@ int binned_sample_step(int m, int n, long long nnz)
 {
     int p0, lb0, q0, sb0;
     count_blocks(m, n, nnz, p0, lb0, q0, sb0);
-    return std::max(1, std::min((m + 65535) / 65536, lb0 / 256));
+    return std::max(1, std::min((int)(((long long)m + 65535) / 65536), lb0 / 256));
 }
 
 bool binned_blocks_sampled(const int *samples, int count, int step, int longest, int m, int n, long long nnz,

@@ -211,6 +211,7 @@ int main()
 {
     check_even_cut();
     check_block_counts();
+    REQUIRE(binned_sample_step(65536, 500000, 5000000) == 1 && binned_sample_step(2147483647, 500000, 2147483647) == 39);
     check_small_blocks();
     for (int kind = 0; kind < 3; ++kind) {
         check_sampled(1000000, 500000, 5000000LL, kind, kind == 0);
