@@ -422,8 +422,9 @@ PMP_BIN_KERNEL void k_bin_link(Dev<T> d)
 // the emission.  One iteration, before -> after: 1e6 links x 5e5 streams,
 // nnz = 5e6: 43.5 -> 37.8 us; 1e6 x 8e5, 8e6: 60.3 -> 47.7; 3e5 x 3e5, 3e6: 30.7
 // -> 25.4; 4e5 x 4e5, 4e6: 29.2; in FP64, 5e6: 65 -> 49.4.  Within a pass at 5e6:
-// 4.7 us until the messages are there, 3.2 adds, 5 rows, 4 messages out, 4.3 to
-// the next kernel's start.  Eight groups in place of five: 38.9 us; the rows'
+// (device clocks, mean over the blocks): 4.8 us until the messages are there, 4.1
+// until every wave has added its own, 1.6 rows, 4.1 messages out, 3.7 to the next
+// kernel's start.  Eight groups in place of five: 38.9 us; the rows'
 // vectors issued with the messages: 40.6.
 constexpr int kOneQuads = 5, kOneStreams = 2, kOneLinks = 4;   // groups of entries, rows a lane
 constexpr size_t kOneLds = 158 * 1024;                          // (160 KiB, less the block sums)
